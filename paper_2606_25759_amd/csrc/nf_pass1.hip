@@ -701,6 +701,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
     // One element group: each worker lives in exactly one wavefront, which
     // stores its own rows of sign words and its own partials, so the block
     // ends without a barrier.
+    if (!active) return;  // 9 to 15 workers: a wavefront without one
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

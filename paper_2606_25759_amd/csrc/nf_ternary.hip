@@ -204,6 +204,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   const int64_t gw0 = (base + e_beg) / 64;
   if (a.eg == 1) {
     // each worker's words were written by its own wavefront only
+    if (!active) return;  // 9 to 15 workers: a wavefront without one
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
