@@ -604,7 +604,8 @@ nf_status nf_endpoint_guard(const nf_endpoint_model* model_host, int64_t n, int6
  * nf_route_bucket and nf_route_buckets record these hipEvent_t handles (each
  * passed as void*) on their stream: before pass 1, after pass 1, after the
  * decision kernel and after pass 2 (the last one also when pass 2 is not
- * needed).  The caller owns the events; passing four NULLs turns recording
+ * needed; a small problem decides and runs its read side in one launch, after
+ * which both are recorded).  The caller owns the events; passing four NULLs turns recording
  * off.  Events are recorded, never synchronised, so calls stay asynchronous.
  */
 nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after_decide,
@@ -614,8 +615,9 @@ nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after
  * Profiling query (no paper counterpart): the number of pass-1 kernel
  * launches that one nf_route_buckets call with these sizes makes (pass 1
  * runs as one launch for a problem of at most 4,096 element chunks, else in
- * launches of a fixed number of chunks, and above 32 workers once per row
- * group).  sign_words = 1
+ * launches of a fixed number of chunks, and above 32 workers, but for the
+ * smallest problems, once per row group or in as many shares of the
+ * chunks).  sign_words = 1
  * for a pass 1 that packs sign words (G-Binary), 0 for one that does not
  * (G-Ternary's first pass, nf_bucket_health), which runs in bigger
  * launches.  0 for n_total = 0 or invalid sizes.  Pure host function.

@@ -147,13 +147,15 @@ void fill_pass1_geometry(const nf::Geometry& geo, nf::Pass1Args* a) {
   } while (0)
 
 // Pass 1 + statistics (and optionally the decision) for buckets of one flat
-// buffer.  Shared by the health, pack and route entry points.
+// buffer.  Shared by the health, pack and route entry points.  With `fused`
+// (its read-side fields set; small_decide(geo)), the decision runs in one
+// launch with the read side.
 nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stride,
                            const uint64_t* mask, uint64_t* bits, int64_t bstride, float* out,
                            int sums, int mean, nf_worker_stats* stats, nf_route_decision* dec,
                            const nf_route_policy* pol, void* ws, hipStream_t s,
                            bool phases = false, const nf::BucketRow* btab = nullptr,
-                           const int32_t* cbucket = nullptr) {
+                           const int32_t* cbucket = nullptr, nf::Small2Args* fused = nullptr) {
   const nf::WorkspaceLayout lay = nf::workspace_layout(geo);
   char* w = static_cast<char*>(ws);
   nf::Pass1Args a;
@@ -200,7 +202,12 @@ nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stri
   d.gs = geo.gs;
   d.groups = geo.groups;
   d.btab = btab;
-  e = nf::launch_decide(geo, d, s);
+  if (fused) {
+    fused->d = d;
+    e = nf::launch_small2(geo, *fused, s);
+  } else {
+    e = nf::launch_decide(geo, d, s);
+  }
   if (e != hipSuccess) return hip_fail(e, "decide launch");
   if (phases) record_phase(2, s);
   return NF_OK;
@@ -248,12 +255,24 @@ nf_status route_geo(const nf::Geometry& geo, const float* g, int64_t stride, int
   const bool ternary = pol->format == NF_FORMAT_TERNARY;
   if (!predecided) NF_TRY(check_bits(bits, bstride, n_total, W));
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const bool fuse = nf::small_decide(geo);
+  nf::Small2Args f;
+  memset(&f, 0, sizeof f);
+  f.bits = bits;
+  f.bstride = bstride;
+  f.counts = counts;
+  f.out = out;
+  f.tau = pol->tau;
+  f.decode_mode = pol->decode_mode;
+  f.mean = pol->fp32_op == NF_FP32_MEAN;
+  f.ternary = ternary || predecided;  // a pass 1 without sign words
+  f.decide_only = predecided;
   // The G-Ternary payload needs each worker's threshold, known only once the
   // bucket has been read: pass 1 then builds no sign payload.
   NF_TRY(run_pass1_decide(geo, g, stride, mask, (predecided || ternary) ? nullptr : bits, bstride, out,
                           predecided ? nf::kSumsAll : nf::kSumsRouted, pol->fp32_op == NF_FP32_MEAN,
-                          stats, dec, pol, ws, s, true, btab, cbucket));
-  if (predecided || n_total == 0) {
+                          stats, dec, pol, ws, s, true, btab, cbucket, fuse ? &f : nullptr));
+  if (predecided || n_total == 0 || fuse) {
     record_phase(3, s);
     return ok();
   }
@@ -354,7 +373,7 @@ nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after
 int64_t nf_pass1_launches(int32_t W, int64_t n_total, int64_t bucket_n, int32_t sign_words) {
   if (W < 1 || W > 255 || n_total <= 0 || bucket_n <= 0) return 0;
   const nf::Geometry geo = nf::make_geometry(W, n_total, bucket_n);
-  return geo.ngroups * nf::ceil_div(geo.total_chunks, nf::pass1_launch_chunks(geo, sign_words != 0));
+  return nf::pass1_launches(geo, sign_words != 0);
 }
 
 int64_t nf_pass1_chunk_elems(int32_t W, int64_t n_total, int64_t bucket_n, int64_t* chunks_per_bucket) {
@@ -976,7 +995,7 @@ nf_status nf_bucket_table_init(int32_t W, const int64_t* bucket_offsets, int32_t
 int64_t nf_pass1_launches_table(int32_t W, const int64_t* bucket_offsets, int32_t nb, int32_t sign_words) {
   if (W < 1 || W > 255 || check_table_offsets(bucket_offsets, nb) != NF_OK) return 0;
   const nf::Geometry geo = nf::make_geometry_table(W, bucket_offsets, nb);
-  return geo.ngroups * nf::ceil_div(geo.total_chunks, nf::pass1_launch_chunks(geo, sign_words != 0));
+  return nf::pass1_launches(geo, sign_words != 0);
 }
 
 size_t nf_workspace_bytes_table(int32_t W, const int64_t* bucket_offsets, int32_t nb) {

@@ -16,12 +16,59 @@ __device__ __forceinline__ bool finite32(float x) {
   return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u;
 }
 
-// Sum over the wavefront by an xor butterfly.  Lane 0 always adds in the
-// same order, so its result is deterministic; callers use lane 0.
+// Wavefront reductions by DPP moves: lane l takes the value of lane l - 1, -2,
+// -4, -8 of its row of 16, then the last lane of the row (of the two rows)
+// before, and 0 where there is none, so that after the step of width s the
+// last lane of every aligned group of 2 s lanes holds the group's sum, added
+// in a fixed order.  A step is a few VALU cycles; the same step through
+// LDS (ds_bpermute) takes some 70 ns, 0.8 us for the two FP64 sums of one
+// worker, which is what a small problem's kernels wait for.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp0(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, true);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp0(double x) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = dpp0<CTRL, ROWS>((uint32_t)u), hi = dpp0<CTRL, ROWS>((uint32_t)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// f(step) with step.template of<T>(x) the partner's x, for every step that
+// groups of `width` lanes (a power of two) take.
+template <int CTRL, int ROWS = 0xf>
+struct DppStep {
+  template <typename T>
+  __device__ __forceinline__ T of(T x) const {
+    return dpp0<CTRL, ROWS>(x);
+  }
+};
+template <typename F>
+__device__ __forceinline__ void group_steps(int width, F f) {
+  if (width > 1) f(DppStep<0x111>{});  // row_shr:1
+  if (width > 2) f(DppStep<0x112>{});
+  if (width > 4) f(DppStep<0x114>{});
+  if (width > 8) f(DppStep<0x118>{});
+  if (width > 16) f(DppStep<0x142, 0xa>{});  // row_bcast:15 into rows 1 and 3
+  if (width > 32) f(DppStep<0x143, 0xc>{});  // row_bcast:31 into rows 2 and 3
+}
+
+// Lane l's value (l the same in every lane), as a scalar.
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const uint64_t u = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double last_lane(double x) { return lane_value(x, 63); }
+
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
-  return x;
+  group_steps(64, [&](auto step) { x += step.of(x); });
+  return last_lane(x);
+}
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+  group_steps(64, [&](auto step) { x += step.of(x); });
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t x) {
@@ -135,16 +182,14 @@ __device__ __forceinline__ XSum xcombine(const XSum& x, const XSum& y) {
   return r;
 }
 
+template <typename STEP>
+__device__ __forceinline__ XSum xstep(const STEP& step, const XSum& x) {
+  return xcombine(x, XSum{step.of(x.s), step.of(x.c), step.of(x.b)});
+}
+
 __device__ __forceinline__ XSum wave_xsum(XSum x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    XSum y;
-    y.s = __shfl_xor(x.s, m, 64);
-    y.c = __shfl_xor(x.c, m, 64);
-    y.b = __shfl_xor(x.b, m, 64);
-    x = xcombine(x, y);
-  }
-  return x;
+  group_steps(64, [&](auto step) { x = xstep(step, x); });
+  return XSum{last_lane(x.s), last_lane(x.c), last_lane(x.b)};
 }
 
 // The FP64 value nearest to the exact total (ties to even) when it is
@@ -290,6 +335,8 @@ __device__ __forceinline__ void lanes_from_ballots(const uint64_t (&bb)[NW], uin
   }
 }
 
+__device__ __forceinline__ int uniform32(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // A wavefront-uniform 64-bit value held in a vector register, as a scalar.
 __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
@@ -341,6 +388,23 @@ __device__ __forceinline__ void bucket_span(int b, const BucketRow* btab, int64_
     len = bucket_len(n_total, bucket_n, b);
     chunk0 = (int64_t)b * slots;
   }
+}
+
+// s + p[0] + p[stride] + ... over n worker rows in order, in FP32, eight rows
+// in flight.
+__device__ __forceinline__ float worker_sum(float s, const float* p, int64_t stride, int n) {
+  int w = 0;
+#pragma unroll 1
+  for (; w + 8 <= n; w += 8, p += 8 * stride) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = p[u * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s = s + x[u];
+  }
+#pragma unroll 1
+  for (; w < n; ++w, p += stride) s = s + *p;
+  return s;
 }
 
 // ------------------------------------------------------ bit-sliced counts

@@ -63,6 +63,7 @@ constexpr int kStageFloats = 16384;      // 64 KiB of LDS
 #endif
 constexpr int kBitsWords = NF_BITS_WORDS;      // LDS words for a chunk's sign words (32 KiB)
 constexpr int kMaxSlots = 512;                 // partials the decision reduces per bucket at most
+constexpr int64_t kDirectPartials = 8192;      // (slots times workers) read without a second level
 // ... above kWideWorkers workers (the decision then reads 64 * W partials
 // per bucket: with 400 of 255 workers each, a 25 MiB bucket's decision
 // took 0.28 ms)
@@ -98,6 +99,13 @@ inline int64_t one_launch_epoch(int64_t total_chunks) {
   return total_chunks <= kOneLaunchChunks ? (total_chunks > 0 ? total_chunks : 1) : kEpochBlocks;
 }
 
+// Small problems take kernels of their own (nf_small.hip): those that get one
+// chunk per compute unit by the rule above.
+// Partials (slots times workers) of a bucket that every read-side block of a
+// small problem reduces for itself; with more, the decision is a launch of
+// its own.  4,096 are 160 KB, read from the caches by each block.
+constexpr int64_t kSmallPartials = 4096;
+
 // Pass 2: a wavefront takes 64 consecutive bitmap words (4096 elements) per
 // step, four wavefronts per block.
 constexpr int kThreads2 = 256;
@@ -112,6 +120,9 @@ constexpr NF_HD int pass1_words(int wpw) { return wpw == 1 ? 8 : wpw == 2 ? 4 : 
 // element group, for NW words per worker and tile.
 constexpr NF_HD int routed_steps(int nw) { return (kMaxG * nw + kWaves - 1) / kWaves; }
 
+// FP32 sums of pass 1: none, at the routed positions, at every position.
+enum SumMode { kSumsNone = 0, kSumsRouted = 1, kSumsAll = 2 };
+
 struct Geometry {
   int W, wg, eg, wpw, T, tile, G;
   int rows, ngroups;     // worker rows of the largest pass-1 group (<= 64), and groups
@@ -119,6 +130,8 @@ struct Geometry {
   bool table;            // buckets from a bucket table (sizes vary)
   int64_t chunks_full;   // chunks of a full bucket (of the largest, for a table)
   int64_t total_chunks;  // over all buckets
+  int64_t total_tiles;   // over all buckets
+  int64_t max_len;       // elements of the largest bucket
   int slots;             // partial-statistics slots per bucket (uniform): one per chunk
   int gs;                // slots per second-level group (0: no second level)
   int groups;            // second-level groups per full bucket (<= kMaxSlots)
@@ -142,6 +155,61 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline int64_t pass1_epoch(const Geometry& g) { return one_launch_epoch(g.total_chunks); }
 inline int64_t pass1_launch_chunks(const Geometry& g, bool sign_words) {
   return sign_words || g.total_chunks <= kOneLaunchChunks ? pass1_epoch(g) : kEpochNoPack;
+}
+
+inline bool small_problem(const Geometry& g) {
+  return g.total_chunks > 0 && g.total_tiles <= kFillChunks &&
+         (int64_t)g.W * g.G * g.tile / 64 <= kBitsWords + kBitsWords / 2;  // all rows' sign words in LDS
+}
+// Gradients up to this size are read with cached loads.
+constexpr int64_t kCachedBytes = 256ll << 20;
+inline int64_t gradient_bytes(const Geometry& g) { return 4 * (int64_t)g.W * g.n_total; }
+// Pass 1 by rows (k_rows) rather than by tiles (k_pass1).  Measured, a step
+// of one bucket by tiles and by rows, with 1% of the elements in short FP32
+// runs ("conv") and with 10% in long ones ("runs"):
+//   W = 8:  64 MB 48.0 -> 41.8 us, 128 MB 57.7 -> 51.2, 256 MB 78.7 -> 83.8 (conv)
+//           64 MB 52.9 -> 43.1 us, 128 MB 64.3 -> 59.0, 256 MB 88.3 -> 96.6 (runs)
+//   W = 64: 256 MB 114 -> 88 us, 1 GB 261 -> 243, 4 GB 890 -> 842 (conv)
+//           256 MB 116 -> 96 us, 1 GB 293 -> 280, 12 GB 2,703 -> 2,732 (runs)
+//   W = 24: 8 GB (several launches by tiles) 3.06 -> 1.70 ms (conv), 1.94 -> 1.87 (runs)
+//   W = 255: 512 MB 297 -> 194 us (conv), 344 -> 219 us (runs)
+// Where bandwidth counts, k_pass1's fast loop reads chunks without a routed
+// element better (W = 32: 2.8 GB of runs 639 us, by rows 690; W = 16, a
+// Transformer's 5.5 GB 1.16 ms, by rows 1.28).  Above 16 workers its mixed
+// chunks go one tile at a time, and in launches of 256 chunks (above
+// kOneLaunchChunks) the slowest of them holds up each launch.
+constexpr int64_t kRowsBytes = 160ll << 20;
+constexpr int64_t kRowsBytesWide = 1ll << 30;  // above 16 workers
+constexpr int64_t kRowsChunks = 12000;         // 17 to 64 workers, above kOneLaunchChunks
+inline bool rows_problem(const Geometry& g) {
+  if (g.total_chunks <= 0) return false;
+  if (small_problem(g) || gradient_bytes(g) <= (g.W <= kWaves ? kRowsBytes : kRowsBytesWide)) return true;
+  return g.W > kWaves && g.W <= kRowGroup && g.total_chunks > kOneLaunchChunks && g.total_chunks <= kRowsChunks;
+}
+inline bool small_decide(const Geometry& g) {
+  return small_problem(g) && g.W <= 64 && g.chunks_full * g.W <= kSmallPartials && g.gs == 0;
+}
+// Pass 1 by rows: items per worker (every parts-th eight of its words each),
+// the fewest that leave at most 7% of the wavefronts' turns idle.
+constexpr int kItems = 256;  // rows times parts at most
+constexpr int kBatch = 8;    // words of a worker in flight together
+inline int pass1_parts(int rows) {
+  int best = 1;
+  double most = 0.0;
+  for (int p = 1; p <= kWaves && rows * p <= kItems; ++p) {
+    const double use = (double)(rows * p) / (double)(kWaves * ceil_div(rows * p, kWaves));
+    if (use >= 0.93) return p;
+    if (use > most) {
+      most = use;
+      best = p;
+    }
+  }
+  return best;
+}
+// Launches of pass 1.
+inline int64_t pass1_launches(const Geometry& g, bool sign_words) {
+  if (rows_problem(g)) return small_problem(g) ? 1 : g.ngroups;
+  return g.ngroups * ceil_div(g.total_chunks, pass1_launch_chunks(g, sign_words));
 }
 
 // Row group i of a geometry: its first worker and its rows (the first
@@ -184,7 +252,8 @@ inline Geometry geometry_core(int W) {
 // kFillChunks tiles.  total_for(G): the problem's chunks at G tiles each.
 template <typename F>
 inline void fill_rule(Geometry& g, F total_for) {
-  const int64_t target = total_for(1) <= kFillChunks ? kSmallFillChunks : kFillChunks;
+  g.total_tiles = total_for(1);
+  const int64_t target = g.total_tiles <= kFillChunks ? kSmallFillChunks : kFillChunks;
   if (total_for(g.G) < target)
     for (int G = 1; G < g.G; ++G)
       if (total_for(G) <= target) {
@@ -204,6 +273,7 @@ inline void slot_groups(Geometry& g, int64_t max_len) {
   const int cap = g.W > kWideWorkers ? kMaxSlotsWide : kMaxSlots;
   g.gs = g.chunks_full > cap ? (int)ceil_div(g.chunks_full, cap) : 0;
   g.groups = g.gs ? (int)ceil_div(g.chunks_full, g.gs) : 0;
+  g.max_len = max_len;
   int64_t words = (max_len + 63) / 64;
   int64_t chunks2 = ceil_div(words, kWordsPerWave2 * 4);
   if (chunks2 < 1) chunks2 = 1;
@@ -295,8 +365,6 @@ inline WorkspaceLayout workspace_layout(const Geometry& g) {
 
 // ------------------------------------------------------- kernel arguments
 
-enum SumMode { kSumsNone = 0, kSumsRouted = 1, kSumsAll = 2 };
-
 struct Pass1Args {
   const float* g;  // the row group's first row
   int64_t wstride;
@@ -308,10 +376,13 @@ struct Pass1Args {
   uint64_t* part_ne;
   int64_t n_total, bucket_n, chunks_full, total_chunks;
   int32_t nb, W, wg, eg, T, G, slots, sums, mean;
-  // Row groups: W is this group's rows; partials are [slot][wtot] with this
-  // group's workers from wbase; racc: the routed FP32 sums continue from
+  // Row groups: W is this group's rows; partials are [slot][wtot] from this
+  // group's first worker on; racc: the routed FP32 sums continue from
   // out (not the first group); rfin: the last group (MEAN divides there).
-  int32_t wtot, wbase, racc, rfin;
+  int32_t wtot, racc, rfin;
+  // Filled by the launcher, for chunks taken by rows: items per worker, LDS
+  // words of a row.
+  int32_t parts, item_words;
   const BucketRow* btab;   // NULL: equal buckets of bucket_n
   const int32_t* cbucket;  // bucket of every chunk (with btab)
 };
@@ -334,6 +405,17 @@ struct DecideArgs {
   int64_t n_total, bucket_n;
   int32_t W, slots, tile, G, gs, groups;
   const BucketRow* btab;  // NULL: equal buckets of bucket_n
+};
+
+// Decision and read side of a small problem (k_small2).
+struct Small2Args {
+  DecideArgs d;
+  uint64_t* bits;  // G-Binary: sign words in; G-Ternary: both planes out
+  int64_t bstride;
+  uint8_t* counts;  // nullable
+  float* out;
+  float tau;
+  int32_t decode_mode, mean, ternary, decide_only;
 };
 
 // kOpFallbackOnly: route-driven, FP32 sums of the buckets routed F only.
@@ -569,8 +651,10 @@ hipError_t launch_cexpand(const ExpandArgs& a, hipStream_t s);
 // Sets the thread-local message of nf_last_error (nf_api.hip) and returns st.
 nf_status set_error(nf_status st, const char* msg);
 
-// Launchers (nf_pass1.hip, nf_pass2.hip, nf_ternary.hip, nf_sliced.hip).
+// Launchers (nf_pass1.hip, nf_rows.hip, nf_small.hip, nf_pass2.hip, nf_ternary.hip, nf_sliced.hip).
 hipError_t launch_pass1(const Geometry& geo, const Pass1Args& a, hipStream_t s);
+hipError_t launch_rows(const Geometry& geo, const Pass1Args& a, hipStream_t s);
+hipError_t launch_small2(const Geometry& geo, const Small2Args& a, hipStream_t s);
 hipError_t launch_decide(const Geometry& geo, const DecideArgs& a, hipStream_t s);
 hipError_t launch_pass2(const Geometry& geo, const Pass2Args& a, hipStream_t s);
 hipError_t launch_ternary_pack(const Geometry& geo, const TernArgs& a, hipStream_t s);

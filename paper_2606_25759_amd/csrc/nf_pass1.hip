@@ -20,33 +20,10 @@
 // streaming scan with a handful of VALU operations per element and worker.
 #include <hip/hip_ext.h>
 
+#include "nf_decide.h"
 #include "nf_device.h"
 
 namespace nf {
-
-// The wavefront's |g| sum of one worker as an XSum: in exact mode from the
-// lanes' (s, c) pairs, otherwise the plain wavefront sum with no error kept.
-template <bool EXACT>
-__device__ __forceinline__ XSum lane_sum(double s, double c, uint32_t nz) {
-  if constexpr (EXACT) return wave_xsum(xlane(s, c, nz));
-  return XSum{wave_sum(s), 0.0, 0.0};
-}
-
-// p += q for partial statistics; in exact mode the |g| sums as XSums, else
-// as plain FP64 sums (their error parts stay 0).
-template <bool EXACT>
-__device__ __forceinline__ void part_add(Partial& p, const Partial& q) {
-  if constexpr (EXACT) {
-    const XSum x = xcombine(XSum{p.sabs, p.sabs_c, p.sabs_b}, XSum{q.sabs, q.sabs_c, q.sabs_b});
-    p.sabs = x.s;
-    p.sabs_c = x.c;
-    p.sabs_b = x.b;
-  } else {
-    p.sabs += q.sabs;
-  }
-  p.ssq += q.ssq;
-  p.nonfinite += q.nonfinite;
-}
 
 // ------------------------------------------------------------------ pass 1
 //
@@ -841,8 +818,7 @@ __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
   __shared__ uint8_t redo[256];            // exact mode: re-sum this worker
   __shared__ unsigned long long hist[256];  // exponent bins of the re-summation
   __shared__ uint64_t ne_s;
-  __shared__ double med_s;
-  __shared__ double qterm[256];  // |g| sum / n_E per worker (the scale's terms)
+  __shared__ DecideScratch scr;
   __shared__ Partial wide[kDecideThreads];  // W > kWideWorkers: [part][W]
   const int b = blockIdx.x;
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront index, uniform
@@ -909,51 +885,14 @@ __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
     if (lane == 0) ne_s = s;
   }
   __syncthreads();
-  // Exact mode: a worker whose rounding the bound could not certify is
-  // summed again from its gradients, exactly (rare: it takes a total within
-  // the bound of a rounding midpoint).
   uint32_t resummed = 0;
-  if (EXACT) {
-    for (int w = 0; w < a.W; ++w) {
-      if (!redo[w]) continue;  // block-uniform
-      const double e = exact_abs_sum(a.g + (int64_t)w * a.wstride, a.mask, base, nbe, hist);
-      if (threadIdx.x == 0) st[w].sum_abs_elig = e;
-      ++resummed;
-    }
-    __syncthreads();
-  }
+  if (EXACT) resummed = resum_exact(st, redo, a, base, nbe, hist);
   for (int w = threadIdx.x; w < a.W; w += kDecideThreads) a.stats[(int64_t)b * a.W + w] = st[w];
   if (!a.dec) return;
-  // The per-worker facts of the route rules, thread t for worker t (W <=
-  // 255): finite sums of squares counted by a block vote, the lower median
-  // by rank, the scale's terms |g| sum / n_E divided in parallel and added
-  // in worker order by one thread (as the host's decision adds them), and
-  // the reason flags by block votes.  (With one thread scanning the workers
-  // the decision of two 255-worker buckets took 88 us; this way, 49 us.)
-  const int t = threadIdx.x;
-  const bool mine = t < a.W;
-  const double ssq = mine ? st[t].sum_sq : 0.0;
-  const double sab = mine ? st[t].sum_abs_elig : 0.0;
-  const bool fin = mine && finite64(ssq);
-  if (t == 0) med_s = 0.0;
-  const int kfin = __syncthreads_count(fin);
-  if (fin && ssq_rank(st, a.W, t) == (kfin - 1) / 2) med_s = ssq;
-  const int64_t ne = (int64_t)ne_s;
-  if (mine) qterm[t] = ne > 0 ? sab / (double)ne : 0.0;
-  const int nonf = __syncthreads_or(mine && st[t].nonfinite != 0);
-  const int zero = __syncthreads_or(mine && sab == 0.0);
-  const int spike = __syncthreads_or(kfin >= 2 && fin && ssq > spike_threshold(a.pol, med_s));
-  if (t == 0) {
-    float scale = 0.0f;
-    if (ne > 0) {
-      double acc = 0.0;
-      for (int w = 0; w < a.W; ++w) acc += qterm[w];
-      scale = (float)(acc / (double)a.W);
-    }
-    nf_route_decision d;
-    decide_finish(nbe, ne, a.pol, nonf != 0, zero != 0, spike != 0, scale, &d);
-    d.resummed = resummed;
-    a.dec[b] = d;
+  if (a.W <= 64) {
+    if (v == 0) decide_wave(st, a.W, nbe, (int64_t)ne_s, a.pol, resummed, &a.dec[b]);
+  } else {
+    decide_block(st, a.W, nbe, (int64_t)ne_s, a.pol, resummed, scr, &a.dec[b]);
   }
 }
 
@@ -999,7 +938,6 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
     if (rows < geo.wg || rows > R) return hipErrorInvalidValue;
     a.W = rows;
     a.wtot = geo.W;
-    a.wbase = wb;
     a.racc = grp > 0;
     a.rfin = grp == geo.ngroups - 1;
     a.g = a0.g + (int64_t)wb * a0.wstride;
@@ -1024,11 +962,16 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
 }
 
 hipError_t launch_pass1(const Geometry& geo, const Pass1Args& a, hipStream_t s) {
+  if (rows_problem(geo)) return launch_rows(geo, a, s);
   return a.bits ? pass1_dispatch<true>(geo, a, s) : pass1_dispatch<false>(geo, a, s);
 }
 
-hipError_t launch_decide(const Geometry& geo, const DecideArgs& a, hipStream_t s) {
-  if (geo.gs > 0) {
+hipError_t launch_decide(const Geometry& geo, const DecideArgs& a0, hipStream_t s) {
+  DecideArgs a = a0;
+  // The second level is a launch of 5 us: the decision reads up to
+  // kDirectPartials itself.
+  if (geo.W <= kWideWorkers && geo.chunks_full * geo.W <= kDirectPartials) a.gs = 0;
+  if (a.gs > 0) {
     if (a.exact)
       hipLaunchKernelGGL(k_slotsum<true>, dim3((unsigned)(geo.nb * geo.groups)), dim3(256), 0, s, a);
     else
