@@ -579,18 +579,25 @@ class Workload:
         nbs = np.diff(self.off)
         ne = d["n_eligible"].astype(np.int64)
         nwb = (nbs + 63) // 64
-        # pass 1: gradients once, mask once, sign words out (G-Binary only), FP32 sums at routed positions out
-        pass1_bytes = float((4 * W * nbs + 8 * nwb + (0 if ternary else 8 * W * nwb) + 4 * (nbs - ne)).sum())
+        # pass 1: gradients once, mask once, sign words out (G-Binary; both planes where G-Ternary takes one read:
+        # 8 workers and 640 MiB on), FP32 sums at routed positions out
+        one_read = ternary and W >= 8 and 4 * W * n > 640 << 20
+        words = 16 * W if one_read else 0 if ternary else 8 * W
+        pass1_bytes = float((4 * W * nbs + 8 * nwb + words * nwb + 4 * (nbs - ne)).sum())
         is_l, is_f = d["route"] == 0, d["route"] == 1
         cbytes = (2 if ternary else 1) * nbs if counts else 0
         if ternary:
-            # second read of the eligible elements, two planes out and back in, mask, counts, decode
-            l_bytes = 4 * W * ne + 8 * nwb + 16 * W * nwb + 16 * W * nwb + 8 * nwb + cbytes + 4 * ne
+            # a second read of the eligible elements that writes two planes (or, after one read, both planes in
+            # to settle their open elements), planes in, mask, counts, decode
+            second = 16 * W * nwb if one_read else 4 * W * ne + 8 * nwb + 16 * W * nwb
+            l_bytes = second + 16 * W * nwb + 8 * nwb + cbytes + 4 * ne
         else:
             l_bytes = 8 * W * nwb + 8 * nwb + cbytes + 4 * ne
         pass2_bytes = float((l_bytes * is_l).sum() + ((4 * W * ne + 8 * nwb + 4 * ne) * is_f).sum())
         launches = (nf.nf_pass1_launches(W, n, self.bn, sign_words=not ternary) if self.bn else
                     nf.nf_pass1_launches_table(W, self.off, sign_words=not ternary))
+        if one_read:  # one launch, or one for each row group
+            launches = 1 if W <= 32 else 2 if W <= 64 else -(-W // 64)
         # a cold run's wall clock includes the overwrites: its value comes from the device events
         value = self.lay.input_bytes() / ((device_ms if cold else ms_per_step) * 1e-3) / 1e9
         plain_value = None if plain_ms is None else self.lay.input_bytes() / (plain_ms * 1e-3) / 1e9

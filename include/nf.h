@@ -400,11 +400,13 @@ nf_status nf_route_decide(const nf_worker_stats* stats_host, int32_t W, int64_t 
  * the policy fixed the route before reading.  counts (nullable): written
  * when the route is L.
  * With policy format NF_FORMAT_TERNARY the low-bit route carries the
- * G-Ternary payload instead: pass 1 builds no sign payload; for route L the
- * per-worker thresholds come from the statistics (nf_ternary_threshold with
- * policy tau), a second read of the eligible elements writes the two planes
+ * G-Ternary payload instead: for route L the per-worker thresholds come from
+ * the statistics (nf_ternary_threshold with policy tau), the two planes go
  * into bits (2W rows, as nf_pack_ternary), and the count and decode of
- * nf_ternary_reduce follow; counts (nullable) then receives 2n bytes.
+ * nf_ternary_reduce follow; counts (nullable) then receives 2n bytes.  A
+ * large problem packs the planes as pass 1 reads, before the thresholds are
+ * known, and corrects them; there, under route F or P decided from the data,
+ * bits is written but holds no payload.
  */
 nf_status nf_route_bucket(const float* grads, int64_t worker_stride, int32_t W, int64_t n,
                           const uint64_t* mask, const nf_route_policy* policy_host,
@@ -619,8 +621,9 @@ nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after
  * smallest problems, once per row group or in as many shares of the
  * chunks).  sign_words = 1
  * for a pass 1 that packs sign words (G-Binary), 0 for one that does not
- * (G-Ternary's first pass, nf_bucket_health), which runs in bigger
- * launches.  0 for n_total = 0 or invalid sizes.  Pure host function.
+ * (G-Ternary's first of two reads, nf_bucket_health), which runs in bigger
+ * launches; one that packs the G-Ternary planes runs as one launch per row
+ * group.  0 for n_total = 0 or invalid sizes.  Pure host function.
  */
 int64_t nf_pass1_launches(int32_t W, int64_t n_total, int64_t bucket_n, int32_t sign_words);
 

@@ -149,16 +149,19 @@ void fill_pass1_geometry(const nf::Geometry& geo, nf::Pass1Args* a) {
 // Pass 1 + statistics (and optionally the decision) for buckets of one flat
 // buffer.  Shared by the health, pack and route entry points.  With `fused`
 // (its read-side fields set; small_decide(geo)), the decision runs in one
-// launch with the read side.
+// launch with the read side.  With `tern` (the whole route's arguments) pass
+// 1 packs the G-Ternary planes.
 nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stride,
                            const uint64_t* mask, uint64_t* bits, int64_t bstride, float* out,
                            int sums, int mean, nf_worker_stats* stats, nf_route_decision* dec,
                            const nf_route_policy* pol, void* ws, hipStream_t s,
                            bool phases = false, const nf::BucketRow* btab = nullptr,
-                           const int32_t* cbucket = nullptr, nf::Small2Args* fused = nullptr) {
+                           const int32_t* cbucket = nullptr, nf::Small2Args* fused = nullptr,
+                           nf::TernArgs* tern = nullptr) {
   const nf::WorkspaceLayout lay = nf::workspace_layout(geo);
   char* w = static_cast<char*>(ws);
   nf::Pass1Args a;
+  memset(&a, 0, sizeof a);
   a.g = g;
   a.wstride = stride;
   a.mask = mask;
@@ -173,7 +176,20 @@ nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stri
   a.sums = sums;
   a.mean = mean;
   if (phases) record_phase(0, s);
-  hipError_t e = nf::launch_pass1(geo, a, s);
+  hipError_t e = hipSuccess;
+  if (tern) {
+    // G-Ternary in one read: the windows first (in stats until the decision
+    // writes it), then pass 1 with both planes.
+    e = nf::launch_ternary_window(geo, *tern, stats, s);
+    if (e != hipSuccess) return hip_fail(e, "ternary window launch");
+    a.bits = tern->bits;
+    a.bstride = tern->bstride;
+    a.nbits = tern->bits + (int64_t)geo.W * tern->bstride;
+    a.win = stats;
+    tern->part = a.part;
+    tern->slots = geo.slots;
+  }
+  e = nf::launch_pass1(geo, a, s);
   if (e != hipSuccess) return hip_fail(e, "pass-1 launch");
   if (phases) record_phase(1, s);
   nf::DecideArgs d;
@@ -183,6 +199,7 @@ nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stri
   d.wstride = stride;
   d.mask = mask;
   d.exact = bits == nullptr;  // pass 1 without sign words tracks exact |g| sums
+  d.windows = tern != nullptr;
   d.stats = stats;
   d.dec = dec;
   if (pol) {
@@ -267,37 +284,36 @@ nf_status route_geo(const nf::Geometry& geo, const float* g, int64_t stride, int
   f.mean = pol->fp32_op == NF_FP32_MEAN;
   f.ternary = ternary || predecided;  // a pass 1 without sign words
   f.decide_only = predecided;
-  // The G-Ternary payload needs each worker's threshold, known only once the
-  // bucket has been read: pass 1 then builds no sign payload.
+  nf::TernArgs t;
+  memset(&t, 0, sizeof t);
+  t.g = g;
+  t.wstride = stride;
+  t.mask = mask;
+  t.bits = bits;
+  t.bstride = bstride;
+  t.dec = dec;
+  t.stats = stats;
+  t.cpos = counts;
+  t.cneg = counts ? counts + n_total : nullptr;
+  t.out = out;
+  t.tau = pol->tau;
+  t.n_total = n_total;
+  t.bucket_n = geo.bucket_n;
+  t.W = W;
+  t.decode_mode = pol->decode_mode;
+  t.bpb2 = geo.bpb2;
+  t.btab = btab;
+  t.cbucket = cbucket;
+  const bool planes = ternary && !predecided && !fuse && nf::planes_in_one_read(geo);
   NF_TRY(run_pass1_decide(geo, g, stride, mask, (predecided || ternary) ? nullptr : bits, bstride, out,
                           predecided ? nf::kSumsAll : nf::kSumsRouted, pol->fp32_op == NF_FP32_MEAN,
-                          stats, dec, pol, ws, s, true, btab, cbucket, fuse ? &f : nullptr));
+                          stats, dec, pol, ws, s, true, btab, cbucket, fuse ? &f : nullptr, planes ? &t : nullptr));
   if (predecided || n_total == 0 || fuse) {
     record_phase(3, s);
     return ok();
   }
   if (ternary) {
-    nf::TernArgs t;
-    memset(&t, 0, sizeof t);
-    t.g = g;
-    t.wstride = stride;
-    t.mask = mask;
-    t.bits = bits;
-    t.bstride = bstride;
-    t.dec = dec;
-    t.stats = stats;
-    t.cpos = counts;
-    t.cneg = counts ? counts + n_total : nullptr;
-    t.out = out;
-    t.tau = pol->tau;
-    t.n_total = n_total;
-    t.bucket_n = geo.bucket_n;
-    t.W = W;
-    t.decode_mode = pol->decode_mode;
-    t.bpb2 = geo.bpb2;
-    t.btab = btab;
-    t.cbucket = cbucket;
-    hipError_t e = nf::launch_ternary_pack(geo, t, s);
+    hipError_t e = planes ? nf::launch_ternary_settle(geo, t, s) : nf::launch_ternary_pack(geo, t, s);
     if (e != hipSuccess) return hip_fail(e, "ternary pack launch");
     e = nf::launch_ternary_reduce(geo, t, s);
     if (e != hipSuccess) return hip_fail(e, "ternary reduce launch");
@@ -454,6 +470,7 @@ nf_status nf_pack_signs(const float* grads, int64_t worker_stride, int32_t W, in
     const nf::WorkspaceLayout lay = nf::workspace_layout(geo);
     char* w = static_cast<char*>(ws);
     nf::Pass1Args a;
+    memset(&a, 0, sizeof a);
     a.g = grads;
     a.wstride = worker_stride;
     a.mask = mask;

@@ -407,6 +407,22 @@ __device__ __forceinline__ float worker_sum(float s, const float* p, int64_t str
   return s;
 }
 
+__device__ __forceinline__ Window load_window(const nf_worker_stats* win, int64_t i) {
+  const float* f = reinterpret_cast<const float*>(win + i);
+  return Window{f[0], f[1]};
+}
+
+// One element a lane into a word of both planes, m the word's mask: kept and
+// gated for sure by the window, both bits where it does not say (see Window).
+__device__ __forceinline__ void tern_words(float x, float lo, float hi, uint64_t m, uint64_t& pos, uint64_t& neg) {
+  const float ax = __builtin_fabsf(x);
+  const uint64_t up = __ballot(x > 0.0f), dn = __ballot(x < 0.0f);
+  const uint64_t low = __ballot(ax < lo), high = __ballot(ax >= hi);
+  const uint64_t open = ~(low | high);
+  pos = ((up & ~low) | open) & m;
+  neg = ((dn & ~low) | open) & m;
+}
+
 // ------------------------------------------------------ bit-sliced counts
 
 struct FullAdd {
@@ -418,10 +434,33 @@ __device__ __forceinline__ FullAdd full_add(uint64_t a, uint64_t b, uint64_t c) 
   return FullAdd{t ^ c, (a & b) | (c & t)};
 }
 
+// Eight words into a bit-sliced counter, through a carry-save tree of full
+// adders (Harley-Seal).  P[b] holds bit b of each element's count, for the
+// nplanes planes that the final counts need.
+__device__ __forceinline__ void count_eight(const uint64_t (&x)[8], int nplanes, uint64_t (&P)[8]) {
+  FullAdd f0 = full_add(P[0], x[0], x[1]);
+  FullAdd f1 = full_add(f0.sum, x[2], x[3]);
+  FullAdd f2 = full_add(P[1], f0.carry, f1.carry);
+  FullAdd f3 = full_add(f1.sum, x[4], x[5]);
+  FullAdd f4 = full_add(f3.sum, x[6], x[7]);
+  FullAdd f5 = full_add(f2.sum, f3.carry, f4.carry);
+  FullAdd f6 = full_add(P[2], f2.carry, f5.carry);
+  P[0] = f4.sum;
+  P[1] = f5.sum;
+  P[2] = f6.sum;
+  uint64_t c = f6.carry;  // weight 8
+#pragma unroll
+  for (int q = 3; q < 8; ++q) {
+    if (q < nplanes) {
+      const uint64_t t = P[q] & c;
+      P[q] ^= c;
+      c = t;
+    }
+  }
+}
+
 // Bit-sliced count of one bitmap word position over W rows (row w at
-// col[w * bstride]): P[b] holds bit b of each element's count, for the
-// nplanes planes that counts 0..W need.  Eight words at a time go through a
-// carry-save tree of full adders (Harley-Seal), the rest ripple in.
+// col[w * bstride]); the rows past the last eight ripple in.
 __device__ __forceinline__ void count_column(const uint64_t* col, int64_t bstride, int W, bool valid,
                                              int nplanes, uint64_t (&P)[8]) {
 #pragma unroll
@@ -431,25 +470,7 @@ __device__ __forceinline__ void count_column(const uint64_t* col, int64_t bstrid
     uint64_t x[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) x[i] = valid ? col[(int64_t)(w + i) * bstride] : 0ull;
-    FullAdd f0 = full_add(P[0], x[0], x[1]);
-    FullAdd f1 = full_add(f0.sum, x[2], x[3]);
-    FullAdd f2 = full_add(P[1], f0.carry, f1.carry);
-    FullAdd f3 = full_add(f1.sum, x[4], x[5]);
-    FullAdd f4 = full_add(f3.sum, x[6], x[7]);
-    FullAdd f5 = full_add(f2.sum, f3.carry, f4.carry);
-    FullAdd f6 = full_add(P[2], f2.carry, f5.carry);
-    P[0] = f4.sum;
-    P[1] = f5.sum;
-    P[2] = f6.sum;
-    uint64_t c = f6.carry;  // weight 8
-#pragma unroll
-    for (int q = 3; q < 8; ++q) {
-      if (q < nplanes) {
-        const uint64_t t = P[q] & c;
-        P[q] ^= c;
-        c = t;
-      }
-    }
+    count_eight(x, nplanes, P);
   }
   for (; w < W; ++w) {
     uint64_t c = valid ? col[(int64_t)w * bstride] : 0ull;

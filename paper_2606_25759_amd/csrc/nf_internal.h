@@ -206,6 +206,17 @@ inline int pass1_parts(int rows) {
   }
   return best;
 }
+// G-Ternary planes in one read (see Window) rather than two: the sample, the
+// planes' stores among pass 1's reads and the open elements cost what a
+// second read of some 600 MB takes.  Steps with two reads and with one: W = 8,
+// 300 MB 190 -> 196 us, 600 MB 314 -> 319, 1.2 GB 570 -> 467; W = 16, 600 MB 316 ->
+// 282 us, 4 GB 1.73 -> 1.36 ms; W = 64, 1.05 GB 473 -> 405 us, 8 GB 3.17 -> 2.45
+// ms; with few workers the count weighs more (W = 2, 1 GB 643 -> 721 us).
+constexpr int64_t kOneReadBytes = 640ll << 20;
+constexpr int kOneReadWorkers = 8;
+inline bool planes_in_one_read(const Geometry& g) {
+  return g.total_chunks > 0 && g.W >= kOneReadWorkers && gradient_bytes(g) > kOneReadBytes;
+}
 // Launches of pass 1.
 inline int64_t pass1_launches(const Geometry& g, bool sign_words) {
   if (rows_problem(g)) return small_problem(g) ? 1 : g.ngroups;
@@ -383,6 +394,10 @@ struct Pass1Args {
   // Filled by the launcher, for chunks taken by rows: items per worker, LDS
   // words of a row.
   int32_t parts, item_words;
+  // G-Ternary (nbits not NULL): bits and nbits are the group's positive and
+  // negative planes, win the [bucket][wtot] windows from its first worker.
+  uint64_t* nbits;
+  const nf_worker_stats* win;
   const BucketRow* btab;   // NULL: equal buckets of bucket_n
   const int32_t* cbucket;  // bucket of every chunk (with btab)
 };
@@ -397,6 +412,7 @@ struct DecideArgs {
   int64_t wstride;
   const uint64_t* mask;
   int32_t exact;
+  int32_t windows;         // G-Ternary: stats holds pass 1's windows until it is written
   Partial* part2;          // second-level sums (gs > 0)
   uint64_t* part2_ne;
   nf_worker_stats* stats;
@@ -421,6 +437,21 @@ struct Small2Args {
 // kOpFallbackOnly: route-driven, FP32 sums of the buckets routed F only.
 enum Pass2Op { kOpCountDecode = 0, kOpFp32 = 1, kOpFromDecision = 2, kOpFallbackOnly = 3 };
 
+// G-Ternary planes in one read (nf_ternary.hip).  A worker's threshold is
+// known only once its whole bucket has been read, so pass 1 packs by a window
+// [lo, hi] that a sample of the bucket puts around it: |g| < lo is gated and
+// |g| >= hi kept for sure, and an element in between (or a NaN) sets its bit
+// in both planes, which no vote does.  Once the threshold is known, those
+// elements are read again and their words corrected.  The windows wait in
+// the first 8 bytes of the bucket's statistics.
+struct Window {
+  float lo, hi;
+};
+static_assert(sizeof(nf_worker_stats) >= sizeof(Window), "a window per worker");
+// Words of a bucket that a worker's sample reads at most (a quarter of them
+// where few blocks take samples, each a chain of reads).
+constexpr int kSampleWords = 4096;
+
 // G-Ternary pack and count/decode.  Route-driven (dec != NULL): only the
 // buckets routed L, thresholds from stats and tau.  Standalone: one bucket,
 // thresholds theta[W] and scale *scale.
@@ -433,6 +464,8 @@ struct TernArgs {
   const nf_route_decision* dec;
   const nf_worker_stats* stats;  // [bucket][W]
   const float* theta;
+  const Partial* part;  // route-driven count: sabs_b of a worker's first partial is 1 if its window missed
+  int32_t slots;
   const float* scale;
   uint8_t* cpos;  // nullable
   uint8_t* cneg;  // nullable
@@ -657,6 +690,8 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a, hipStream_t s);
 hipError_t launch_small2(const Geometry& geo, const Small2Args& a, hipStream_t s);
 hipError_t launch_decide(const Geometry& geo, const DecideArgs& a, hipStream_t s);
 hipError_t launch_pass2(const Geometry& geo, const Pass2Args& a, hipStream_t s);
+hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a, nf_worker_stats* win, hipStream_t s);
+hipError_t launch_ternary_settle(const Geometry& geo, const TernArgs& a, hipStream_t s);
 hipError_t launch_ternary_pack(const Geometry& geo, const TernArgs& a, hipStream_t s);
 hipError_t launch_ternary_reduce(const Geometry& geo, const TernArgs& a, hipStream_t s);
 hipError_t launch_psum(const PsumArgs& a, hipStream_t s);

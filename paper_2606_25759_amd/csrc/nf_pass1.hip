@@ -36,7 +36,7 @@ namespace nf {
 // per wavefront with sign words; four without (the exact |g| sums need a few
 // registers more, and at 64 they spilled: G-Ternary's first pass at GPT
 // scale 23.2 ms against 13.6 ms at four) or with more workers.
-template <int WPW, bool PACK>
+template <int WPW, bool PACK, bool TERN>
 __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <= 2 && PACK ? 8 : 4, WPW <= 2 && PACK ? 8 : 4))) void k_pass1(
     const float* __restrict__ g, const uint64_t* __restrict__ mask, uint64_t* __restrict__ bits,
     float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, Pass1Args a,
@@ -65,7 +65,8 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   // LDS: the chunk's sign words [W][G * EG * NW], then the FP32 stage [W][tile]
   const int cw = a.G * a.eg * NW;  // sign words per worker and chunk
   uint64_t* wbuf = reinterpret_cast<uint64_t*>(smem);
-  const size_t stage_off = PACK ? (size_t)a.W * cw * sizeof(uint64_t) : 0;
+  uint64_t* nbuf = wbuf + (size_t)a.W * cw;  // TERN: the negative planes'
+  const size_t stage_off = (PACK ? 1 : TERN ? 2 : 0) * (size_t)a.W * cw * sizeof(uint64_t);
   float* stage = reinterpret_cast<float*>(smem + stage_off);
   // then the chunk's mask words [G * EG * NW] (mixed chunks)
   uint64_t* mwords =
@@ -76,6 +77,26 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   // the mean divides by all workers after the last group.
   auto sum_first = [&](int64_t pos, float x0) { return a.racc ? out[pos] + x0 : x0; };
   auto sum_last = [&](float s) { return a.mean && a.rfin ? s / (float)a.wtot : s; };
+
+  // G-Ternary: the windows of this wavefront's workers (see tern_words).
+  float wlo[WPW], whi[WPW];
+  if constexpr (TERN) {
+#pragma unroll
+    for (int j = 0; j < WPW; ++j) {
+      const int w = wg + j * a.wg;
+      const Window wd = load_window(a.win, (int64_t)b * a.wtot + (w < a.W ? w : wg));
+      wlo[j] = wd.lo;
+      whi[j] = wd.hi;
+    }
+  }
+  // Word k of this lane's NW of worker w's planes from word `at` of the chunk on.
+  auto put_planes = [&](int w, int at, const uint64_t (&pb)[NW], const uint64_t (&nb)[NW], int words) {
+    uint32_t lo, hi;
+    lanes_from_ballots<NW>(pb, lo, hi);
+    if (lane < words) wbuf[w * cw + at + lane] = ((uint64_t)hi << 32) | lo;
+    lanes_from_ballots<NW>(nb, lo, hi);
+    if (lane < words) nbuf[w * cw + at + lane] = ((uint64_t)hi << 32) | lo;
+  };
 
   // Per-worker health of this lane.  Exact mode (no sign words): sabs[j] +
   // sabc[j] is the lane's exact |g| sum (TwoSum per term).
@@ -268,11 +289,12 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if (st >= nsteps) break;
         out[c0 + (int64_t)st * 64 + lane] = sum_last(run[i]);
       }
-      if (PACK) {
+      if (PACK || TERN) {
         const int64_t gw0 = c0 / 64;
         for (int i = threadIdx.x; i < a.W * nsteps; i += kThreads1) {
           const int w = i / nsteps;
           bits[(int64_t)w * a.bstride + gw0 + (i - w * nsteps)] = 0ull;
+          if (TERN) a.nbits[(int64_t)w * a.bstride + gw0 + (i - w * nsteps)] = 0ull;
         }
       }
       if (threadIdx.x == 0) part_ne[slot] = 0;
@@ -320,11 +342,12 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       }
     }
     // Zero sign words for the chunk, row by row.
-    if (PACK) {
+    if (PACK || TERN) {
       const int64_t gw0 = c0 / 64;
       for (int i = threadIdx.x; i < a.W * nsteps; i += kThreads1) {
         const int w = i / nsteps;
         bits[(int64_t)w * a.bstride + gw0 + (i - w * nsteps)] = 0ull;
+        if (TERN) a.nbits[(int64_t)w * a.bstride + gw0 + (i - w * nsteps)] = 0ull;
       }
     }
     // Block partials: wavefront sums, then wavefronts in order.
@@ -383,6 +406,12 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         s2 = __builtin_fma(d, d, s2);
         s1 += __builtin_fabs(d);
         if constexpr (EXACT) umt = term_umin(umt, x[k]);
+      }
+      if constexpr (TERN) {
+        uint64_t pb[NW], nb[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], ~0ull, pb[k], nb[k]);
+        put_planes(w, (ti * a.eg + eg) * NW, pb, nb, NW);
       }
       if constexpr (EXACT) tile_into_lane<NW>(sabs[j], sabc[j], snz[j], um[j], tw[j], s1, umt, rp[j] + t * tile, ~0u);
       if (PACK) {
@@ -462,6 +491,12 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
             const bool el = (mw[k] >> lane) & 1ull;
             s1 += el ? __builtin_fabs(d) : 0.0;
             if constexpr (EXACT) umt = term_umin(umt, el ? x[k] : 0.0f);
+          }
+          if constexpr (TERN) {
+            uint64_t pb[NW], nb[NW];
+#pragma unroll
+            for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
+            put_planes(w, (ti * a.eg + eg) * NW, pb, nb, NW);
           }
           if constexpr (EXACT) {
             uint32_t el = 0;
@@ -628,6 +663,12 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
             if constexpr (EXACT) umt = term_umin(umt, el ? x[k] : 0.0f);
           }
         }
+        if constexpr (TERN) {
+          uint64_t pb[NW], nb[NW];
+#pragma unroll
+          for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
+          put_planes(w, (int)((t - tb) * a.eg + eg) * NW, pb, nb, nwv < NW ? nwv : NW);
+        }
         if constexpr (EXACT) {
           uint32_t el = 0;
 #pragma unroll
@@ -692,6 +733,11 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       if (w >= a.W) break;
       if (PACK)
         for (int o = lane; o < valid; o += 64) bits[(int64_t)w * a.bstride + gw0 + o] = wbuf[w * cw + o];
+      if (TERN)
+        for (int o = lane; o < valid; o += 64) {
+          bits[(int64_t)w * a.bstride + gw0 + o] = wbuf[w * cw + o];
+          a.nbits[(int64_t)w * a.bstride + gw0 + o] = nbuf[w * cw + o];
+        }
       const XSum x1 = lane_sum<EXACT>(sabs[j], sabc[j], snz[j]);
       const double s2 = wave_sum(ssq[j]);
       if (lane == 0) {
@@ -710,7 +756,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
 
   __syncthreads();
   // The chunk's sign words, row by row, as coalesced stores.
-  if (PACK && te > tb) {
+  if ((PACK || TERN) && te > tb) {
     const int64_t e_beg = tb * tile;
     const int64_t e_end = (te * tile < nbe) ? te * tile : nbe;
     const int valid = (int)((e_end - e_beg + 63) / 64);
@@ -719,6 +765,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       const int w = i / valid;
       const int o = i - w * valid;
       bits[(int64_t)w * a.bstride + gw0 + o] = wbuf[w * cw + o];
+      if (TERN) a.nbits[(int64_t)w * a.bstride + gw0 + o] = nbuf[w * cw + o];
     }
     __syncthreads();
   }
@@ -887,7 +934,17 @@ __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
   __syncthreads();
   uint32_t resummed = 0;
   if (EXACT) resummed = resum_exact(st, redo, a, base, nbe, hist);
-  for (int w = threadIdx.x; w < a.W; w += kDecideThreads) a.stats[(int64_t)b * a.W + w] = st[w];
+  for (int w = threadIdx.x; w < a.W; w += kDecideThreads) {
+    if (a.windows) {
+      // G-Ternary: did the worker's threshold fall into the window that pass
+      // 1 packed its planes by?  The answer takes a dead field of its first
+      // partial.
+      const Window wd = load_window(a.stats, (int64_t)b * a.W + w);
+      const float theta = ternary_threshold(st[w], (int64_t)ne_s, a.pol.tau);
+      const_cast<Partial*>(a.part)[chunk0 * a.W + w].sabs_b = (wd.lo <= theta && theta <= wd.hi) ? 0.0 : 1.0;
+    }
+    a.stats[(int64_t)b * a.W + w] = st[w];
+  }
   if (!a.dec) return;
   if (a.W <= 64) {
     if (v == 0) decide_wave(st, a.W, nbe, (int64_t)ne_s, a.pol, resummed, &a.dec[b]);
@@ -898,12 +955,12 @@ __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
 
 // --------------------------------------------------------------- launchers
 
-template <bool PACK>
+template <bool PACK, bool TERN>
 static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipStream_t s) {
   const dim3 block(kThreads1);
   const int R = geo.rows;  // workers of the largest row group
   const int cw = geo.G * geo.eg * pass1_words(geo.wpw);
-  size_t smem = PACK ? (size_t)R * cw * sizeof(uint64_t) : 0;
+  size_t smem = (PACK ? 1 : TERN ? 2 : 0) * (size_t)R * cw * sizeof(uint64_t);
   if (a0.sums != kSumsNone) smem += (size_t)R * geo.tile * sizeof(float);
   smem += (size_t)geo.G * geo.eg * pass1_words(geo.wpw) * sizeof(uint64_t);  // mask words of a mixed chunk
   size_t red = (size_t)geo.eg * R * sizeof(Partial) + (size_t)geo.eg * sizeof(uint64_t);
@@ -915,9 +972,9 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
     // Above 64 KiB of dynamic LDS the kernel must opt in (gfx950 has 160 KiB per CU).
     hipError_t e = hipSuccess;
     switch (geo.wpw) {
-      case 1: e = hipFuncSetAttribute((const void*)k_pass1<1, PACK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
-      case 2: e = hipFuncSetAttribute((const void*)k_pass1<2, PACK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
-      case 4: e = hipFuncSetAttribute((const void*)k_pass1<4, PACK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
+      case 1: e = hipFuncSetAttribute((const void*)k_pass1<1, PACK, TERN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
+      case 2: e = hipFuncSetAttribute((const void*)k_pass1<2, PACK, TERN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
+      case 4: e = hipFuncSetAttribute((const void*)k_pass1<4, PACK, TERN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); break;
       default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
@@ -929,7 +986,7 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
   // ordered too when it continues the FP32 sums in the output.  The next
   // ordered launch (the decision) waits for all.
   const uint32_t overlap = hipExtAnyOrderLaunch;
-  const int64_t epoch = pass1_launch_chunks(geo, PACK);
+  const int64_t epoch = TERN ? (geo.total_chunks > 0 ? geo.total_chunks : 1) : pass1_launch_chunks(geo, PACK);
   for (int grp = 0; grp < geo.ngroups; ++grp) {
     Pass1Args a = a0;
     int wb, rows;
@@ -942,6 +999,10 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
     a.rfin = grp == geo.ngroups - 1;
     a.g = a0.g + (int64_t)wb * a0.wstride;
     if (a0.bits) a.bits = a0.bits + (int64_t)wb * a0.bstride;
+    if (TERN) {
+      a.nbits = a0.nbits + (int64_t)wb * a0.bstride;
+      a.win = a0.win + wb;
+    }
     a.part = a0.part + wb;
     const bool chained = grp > 0 && a0.sums != kSumsNone;
     for (int64_t q0 = 0; q0 < geo.total_chunks; q0 += epoch) {
@@ -949,9 +1010,9 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
       const dim3 grid((unsigned)(left < epoch ? left : epoch));
       const uint32_t fl = (q0 == 0 && (grp == 0 || chained)) ? 0u : overlap;
       switch (geo.wpw) {
-        case 1: hipExtLaunchKernelGGL((k_pass1<1, PACK>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
-        case 2: hipExtLaunchKernelGGL((k_pass1<2, PACK>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
-        case 4: hipExtLaunchKernelGGL((k_pass1<4, PACK>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
+        case 1: hipExtLaunchKernelGGL((k_pass1<1, PACK, TERN>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
+        case 2: hipExtLaunchKernelGGL((k_pass1<2, PACK, TERN>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
+        case 4: hipExtLaunchKernelGGL((k_pass1<4, PACK, TERN>), grid, block, smem, s, nullptr, nullptr, fl, a.g, a.mask, a.bits, a.out, a.part, a.part_ne, a, q0); break;
         default: return hipErrorInvalidValue;
       }
       const hipError_t e = hipGetLastError();
@@ -963,7 +1024,8 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
 
 hipError_t launch_pass1(const Geometry& geo, const Pass1Args& a, hipStream_t s) {
   if (rows_problem(geo)) return launch_rows(geo, a, s);
-  return a.bits ? pass1_dispatch<true>(geo, a, s) : pass1_dispatch<false>(geo, a, s);
+  if (a.nbits) return pass1_dispatch<false, true>(geo, a, s);
+  return a.bits ? pass1_dispatch<true, false>(geo, a, s) : pass1_dispatch<false, false>(geo, a, s);
 }
 
 hipError_t launch_decide(const Geometry& geo, const DecideArgs& a0, hipStream_t s) {

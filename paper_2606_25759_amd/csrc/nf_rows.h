@@ -28,8 +28,8 @@ __device__ __forceinline__ void put_partial(Partial& p, const XSum& x, double ss
 // LDS stage, and no barrier between the wavefronts but one at the end.
 // red and red_ne: LDS for kItems partials and kWaves counts.
 
-template <bool PACK, bool SMALL, bool CACHED>
-__device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int64_t e0, int len, uint64_t* lds,
+template <bool PACK, bool TERN, bool SMALL, bool CACHED>
+__device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int b, int64_t e0, int len, uint64_t* lds,
                                               Partial* red, uint32_t* red_ne) {
   constexpr bool EXACT = !PACK;
   constexpr int NW = kBatch;
@@ -47,7 +47,13 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
   auto put_row = [&](int w, const uint64_t* words) {
     uint64_t* to = a.bits + (int64_t)w * a.bstride + e0 / 64;
     for (int i = lane; i < nwc; i += 64) to[i] = words[i];
+    if (TERN) {
+      to = a.nbits + (int64_t)w * a.bstride + e0 / 64;
+      for (int i = lane; i < nwc; i += 64) to[i] = words[a.item_words + i];
+    }
   };
+  constexpr int ROWS = TERN ? 2 : 1;  // LDS rows per worker: sign words, or both planes'
+
 
   for (int it = v; it < W * parts; it += kWaves) {
     int w = it, part = 0;
@@ -56,7 +62,9 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
       ++part;
     }
     const float* row = g0 + (int64_t)w * a.wstride;
-    uint64_t* words = lds + (parts == 1 ? v : w) * a.item_words;
+    uint64_t* words = lds + (parts == 1 ? v : w) * ROWS * a.item_words;
+    Window wd{0.0f, 0.0f};
+    if (TERN) wd = load_window(a.win, (int64_t)b * a.wtot + w);
     double sabs = 0.0, sabc = 0.0, ssq = 0.0;
     uint32_t snz = 0, uml = ~0u;
     bool tw = false;
@@ -68,12 +76,13 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
     auto examine = [&](int k, const float (&x)[NW], uint64_t mv) {
       double s1 = 0.0, s2 = 0.0;
       uint32_t umt = ~0u, el8 = 0;
-      uint64_t bb[NW];
+      uint64_t bb[NW], nb[NW];
 #pragma unroll
       for (int u = 0; u < NW; ++u) {
         const uint64_t m = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(mv >> 32), u) << 32) |
                            (uint32_t)__builtin_amdgcn_readlane((uint32_t)mv, u);
         if (PACK) bb[u] = __ballot(x[u] > 0.0f) & m;
+        if (TERN) tern_words(x[u], wd.lo, wd.hi, m, bb[u], nb[u]);
         const bool el = __builtin_amdgcn_inverse_ballot_w64(m);
         const double d = (double)x[u];
         s2 = __builtin_fma(d, d, s2);
@@ -91,10 +100,14 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
         for (int u = 0; u < NW; ++u) nonf += __popcll(__ballot(!finite32(x[u])));
       }
       if (w == 0 && lane < NW) ne += __popcll(mv);
-      if (PACK) {
+      if (PACK || TERN) {
         uint32_t lo, hi;
         lanes_from_ballots<NW>(bb, lo, hi);
         if (lane < NW) words[k + lane] = ((uint64_t)hi << 32) | lo;
+        if (TERN) {
+          lanes_from_ballots<NW>(nb, lo, hi);
+          if (lane < NW) words[a.item_words + k + lane] = ((uint64_t)hi << 32) | lo;
+        }
       }
     };
     // Words k .. k + 7 and, in lanes 0 .. 7, their mask words.  In the chunk's
@@ -149,7 +162,7 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
         examine(k, x, mv);
       }
     }
-    if (PACK && parts == 1) {
+    if ((PACK || TERN) && parts == 1) {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -191,8 +204,8 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
 
   if (parts > 1) {
     __syncthreads();
-    if (PACK)
-      for (int w = v; w < W; w += kWaves) put_row(w, lds + w * a.item_words);
+    if (PACK || TERN)
+      for (int w = v; w < W; w += kWaves) put_row(w, lds + w * ROWS * a.item_words);
     const int w = threadIdx.x;
     if (w < W) {
       Partial p = red[w];

@@ -7,7 +7,7 @@
 namespace nf {
 
 // A block takes chunk q0 + blockIdx.x, all its rows.
-template <bool PACK, bool SMALL, bool CACHED>
+template <bool PACK, bool TERN, bool SMALL, bool CACHED>
 __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(PACK ? 8 : 4, 8))) void k_rows(
     Pass1Args a, int64_t q0) {
   extern __shared__ uint64_t lds[];  // sign words: see chunk_by_rows
@@ -21,14 +21,17 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(PACK 
   const int64_t ch = (int64_t)a.G * a.eg * a.T;  // elements of a whole chunk
   const int64_t e0 = base + c * ch;
   const int len = (int)(nbe - c * ch < ch ? nbe - c * ch : ch);  // >= 1
-  chunk_by_rows<PACK, SMALL, CACHED>(a, q, e0, len, lds, red, red_ne);
+  chunk_by_rows<PACK, TERN, SMALL, CACHED>(a, q, b, e0, len, lds, red, red_ne);
 }
 
 hipError_t launch_rows(const Geometry& geo, const Pass1Args& a0, hipStream_t s) {
   const bool small = small_problem(geo);
   const bool cached = small || gradient_bytes(geo) <= kCachedBytes;
-  const auto kernel = a0.bits ? (small ? k_rows<true, true, true> : cached ? k_rows<true, false, true> : k_rows<true, false, false>)
-                              : (small ? k_rows<false, true, true> : cached ? k_rows<false, false, true> : k_rows<false, false, false>);
+  const bool tern = a0.nbits != nullptr, pack = a0.bits && !tern;
+  const auto kernel =
+      tern ? (cached ? k_rows<false, true, false, true> : k_rows<false, true, false, false>)
+      : pack ? (small ? k_rows<true, false, true, true> : cached ? k_rows<true, false, false, true> : k_rows<true, false, false, false>)
+             : (small ? k_rows<false, false, true, true> : cached ? k_rows<false, false, false, true> : k_rows<false, false, false, false>);
   Pass1Args a = a0;
   a.wtot = geo.W;
   a.item_words = (int)(ceil_div((int64_t)geo.G * geo.tile / 64, kBatch) * kBatch);
@@ -53,12 +56,21 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a0, hipStream_t s) 
     a.rfin = wb + rows == geo.W;
     a.g = a0.g + (int64_t)wb * a0.wstride;
     if (a0.bits) a.bits = a0.bits + (int64_t)wb * a0.bstride;
+    if (tern) {
+      a.nbits = a0.nbits + (int64_t)wb * a0.bstride;
+      a.win = a0.win + wb;
+    }
     a.part = a0.part + wb;
     a.parts = pass1_parts(rows);
     // sign words: a row for each wavefront, or (several items a worker) for
     // each worker
-    const size_t lds = a.bits ? (size_t)(a.parts == 1 ? kWaves : rows) * a.item_words * sizeof(uint64_t) : 0;
-    if (lds + kItems * sizeof(Partial) + 1024 > 65536) return hipErrorInvalidValue;
+    const size_t lds =
+        (size_t)((pack ? 1 : tern ? 2 : 0) * (a.parts == 1 ? kWaves : rows)) * a.item_words * sizeof(uint64_t);
+    if (lds > 65536 - kItems * sizeof(Partial) - 1024) {
+      // above 64 KiB of LDS a kernel must opt in (gfx950 has 160 KiB per CU)
+      const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
     const bool ordered = i == 0 || (by_group && a.sums != kSumsNone);
     hipExtLaunchKernelGGL(kernel, dim3((unsigned)(q1 - q0)), dim3(kThreads1), lds, s, nullptr, nullptr,
                           ordered ? 0u : (uint32_t)hipExtAnyOrderLaunch, a, q0);

@@ -1,6 +1,11 @@
 // nf_ternary.hip - G-Ternary write side and count/decode (§2.2; gfx950).
 //
-//   k_tpack   both planes per worker, laid out as pass 1's chunks
+//   k_twindow a sample of every bucket and worker: the window around its
+//             threshold by which pass 1 packs the planes as it reads
+//   k_tsettle the elements that the window left open, read again
+//   k_tpack   both planes per worker from given thresholds, laid out as
+//             pass 1's chunks: in a second read of the gradients, or from
+//             given thresholds (nf_pack_ternary)
 //   k_tpass2  pass 2's bit-sliced counter over the positive and the negative
 //             planes, decoded from their difference
 #include <hip/hip_ext.h>
@@ -8,6 +13,98 @@
 #include "nf_device.h"
 
 namespace nf {
+
+// ------------------------------------------------------- threshold windows
+//
+// Block (worker, bucket): the mean |g| of a sample of the worker's eligible
+// elements, at most `most` words, one from each of as many stretches of
+// the bucket (so that every parameter's scale is met), at a place of its own
+// in each.  The threshold is tau times the whole bucket's mean; with S1 and
+// S2 the sample's sums of |g| and g*g, a mean over independent elements is
+// off by less than sqrt(S2) / S1 of itself (one deviation; for normal values
+// 1.25 / sqrt(m), and truly 0.75 / sqrt(m)), and the window is two of these
+// wide on either side: about 0.5% of theta for 262,144 elements, which leaves
+// 0.3% of normally distributed elements open.  A threshold outside its window
+// costs a second read of that worker's rows, not a result.
+__global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_stats* win, int most) {
+  __shared__ double r1[kWaves], r2[kWaves];
+  __shared__ uint32_t rn[kWaves];
+  const int w = blockIdx.x, b = blockIdx.y;
+  const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  int64_t base, nbe, chunk0;
+  bucket_span(b, a.btab, a.n_total, a.bucket_n, 0, base, nbe, chunk0);
+  const float* row = a.g + (int64_t)w * a.wstride + base;
+  const int64_t nw = (nbe + 63) / 64;
+  int64_t ns = nw <= 64 ? nw : nw / 24;  // sampled words: 4%, 64 to `most`
+  if (nw > 64 && ns < 64) ns = 64;
+  if (ns > most) {
+    // few blocks: a large bucket's window is worth a longer sample
+    const int64_t more = most < kSampleWords ? nw / 64 : 0;
+    ns = more > most ? (more < 4 * kSampleWords ? more : 4 * kSampleWords) : most;
+  }
+  double s1 = 0.0, s2 = 0.0;
+  uint32_t n = 0;
+  constexpr int NL = 16;  // words in flight
+#pragma unroll 1
+  for (int64_t j0 = v * 64; j0 < ns; j0 += kThreads1) {
+    // this lane's sampled word, from stretch j of ns, and its mask word
+    const int64_t j = j0 + lane;
+    int64_t k = 0;
+    uint64_t m = 0;
+    if (j < ns) {
+      k = (j * nw + (int64_t)((uint32_t)j * 2654435761u >> 8) % nw) / ns;
+      m = a.mask[base / 64 + k] & low_bits(nbe - 64 * k);
+    }
+    n += (uint32_t)__popcll(m);
+    const int mine = ns - j0 < 64 ? (int)(ns - j0) : 64;  // words of this wavefront
+#pragma unroll 1
+    for (int i = 0; i < mine; i += NL) {
+      float x[NL];
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        const int64_t e = 64 * (int64_t)__builtin_amdgcn_readlane((int)k, i + u) + lane;
+        x[u] = row[e < nbe ? e : nbe - 1];
+      }
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        const uint64_t mu = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(m >> 32), i + u) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((uint32_t)m, i + u);
+        const bool el = __builtin_amdgcn_inverse_ballot_w64(mu) && finite32(x[u]);
+        const double d = el ? (double)x[u] : 0.0;
+        s1 += __builtin_fabs(d);
+        s2 = __builtin_fma(d, d, s2);
+      }
+    }
+  }
+  s1 = wave_sum(s1);
+  s2 = wave_sum(s2);
+  n = wave_sum_u32(n);
+  if (lane == 0) {
+    r1[v] = s1;
+    r2[v] = s2;
+    rn[v] = n;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t1 = 0.0, t2 = 0.0, tn = 0.0;
+    for (int i = 0; i < kWaves; ++i) {
+      t1 += r1[i];
+      t2 += r2[i];
+      tn += (double)rn[i];
+    }
+    // a point where the sample says too little: the worker is read again
+    double theta = 0.0, eps = 0.0;
+    if (t1 > 0.0) {
+      theta = (double)a.tau * (t1 / tn);
+      eps = ns == nw ? 1e-5 : 2.0 * sqrt(t2) / t1;
+      if (!(eps < 0.25)) eps = 0.0;
+    }
+    float* f = reinterpret_cast<float*>(win + (int64_t)b * a.W + w);
+    f[0] = (float)(theta * (1.0 - eps));
+    f[1] = (float)(theta * (1.0 + eps));
+  }
+}
 
 // ---------------------------------------------------------------- G-Ternary
 //
@@ -228,6 +325,133 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   }
 }
 
+// --------------------------------------------------------- open elements
+//
+// Block (words, bucket, worker) of a bucket routed L: a wavefront takes 256
+// words of one worker, lane l words l, 64 + l, ...  An element that stands in
+// both planes (pass 1's window left it open) is read again and keeps or loses
+// its bits by the threshold.  What bounds it are single reads all over the
+// gradients, each some microseconds away: the wavefront first lists its open
+// elements in LDS (some 80 of 16,384), then reads them all at once, a lane
+// an element.  (Lane by lane, a bit of each of its words a round, 25 MiB of 8
+// workers took 39 us.)  The rows of a worker whose threshold missed its
+// window are read whole and packed anew.
+constexpr int kOpenList = 512;  // open elements listed at a time
+
+__global__ __launch_bounds__(kThreads2) void k_tsettle(TernArgs a) {
+  constexpr int NU = 4;
+  __shared__ uint64_t pw[kThreads2 / 64][64 * NU], nv[kThreads2 / 64][64 * NU];
+  __shared__ uint16_t list[kThreads2 / 64][kOpenList];
+  const int b = blockIdx.y, w = blockIdx.z;
+  if (a.dec[b].route != NF_ROUTE_LOWBIT) return;  // whole block
+  int64_t base, nbe, chunk0;
+  bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
+  const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (nbe + 63) / 64;
+  const int64_t k0 = ((int64_t)blockIdx.x * (kThreads2 / 64) + v) * 64 * NU;
+  if (k0 >= nw) return;  // whole wavefront
+  uint64_t* prow = a.bits + (int64_t)w * a.bstride + base / 64;
+  uint64_t* nrow = prow + (int64_t)a.W * a.bstride;
+  const float* row = a.g + (int64_t)w * a.wstride + base;
+  const float th = ternary_threshold(a.stats[(int64_t)b * a.W + w], a.dec[b].n_eligible, a.tau);
+  if (a.part[chunk0 * a.W + w].sabs_b == 0.0) {
+    uint64_t open[NU];
+    uint32_t dirty = 0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int64_t k = k0 + 64 * u + lane;
+      const uint64_t p = k < nw ? prow[k] : 0ull;
+      const uint64_t n = k < nw ? nrow[k] : 0ull;
+      pw[v][64 * u + lane] = p;
+      nv[v][64 * u + lane] = n;
+      open[u] = p & n;
+      dirty |= (open[u] != 0 ? 1u : 0u) << u;
+    }
+    if (!__any(dirty != 0)) return;
+    while (true) {
+      // list the open elements, as many as fit: lane l's after lane l - 1's
+      int cnt = 0;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) cnt += __popcll(open[u]);
+      int at = cnt;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int y = __shfl_up(at, d, 64);
+        if (lane >= d) at += y;
+      }
+      const int total = __builtin_amdgcn_readlane(at, 63);
+      if (total == 0) break;
+      at -= cnt;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        while (open[u] != 0 && at < kOpenList) {
+          list[v][at++] = (uint16_t)((64 * u + lane) * 64 + __builtin_ctzll(open[u]));
+          open[u] &= open[u] - 1;
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const int listed = total < kOpenList ? total : kOpenList;
+      for (int i = lane; i < listed; i += 2 * 64) {
+        const bool two = i + 64 < listed;
+        const uint32_t e0 = list[v][i], e1 = list[v][two ? i + 64 : i];
+        const float x0 = __builtin_nontemporal_load(row + 64 * k0 + e0);
+        const float x1 = __builtin_nontemporal_load(row + 64 * k0 + e1);
+        auto settle = [&](uint32_t e, float x) {
+          const uint64_t others = ~(1ull << (e & 63));
+          const bool keep = !(__builtin_fabsf(x) < th);
+          if (!(keep && x > 0.0f)) atomicAnd((unsigned long long*)&pw[v][e >> 6], others);
+          if (!(keep && x < 0.0f)) atomicAnd((unsigned long long*)&nv[v][e >> 6], others);
+        };
+        settle(e0, x0);
+        if (two) settle(e1, x1);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if ((dirty >> u) & 1u) {
+        prow[k0 + 64 * u + lane] = pw[v][64 * u + lane];
+        nrow[k0 + 64 * u + lane] = nv[v][64 * u + lane];
+      }
+    return;
+  }
+  const uint64_t* mrow = a.mask + base / 64;
+#pragma unroll 1
+  for (int64_t k1 = k0; k1 < k0 + 64 * NU && k1 < nw; k1 += 64) {
+    const int64_t left = nbe - 64 * k1;  // elements from word k1 on
+    const bool valid = k1 + lane < nw;
+    const uint64_t mw = valid ? mrow[k1 + lane] & low_bits(left - 64 * lane) : 0ull;
+    uint64_t p = 0, n = 0;
+#pragma unroll 1
+    for (int k = 0; k < 64 && 64 * k < left; k += 8) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int64_t e = 64 * (k + i) + lane;
+        x[i] = row[64 * k1 + (e < left ? e : left - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint64_t m = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(mw >> 32), k + i) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((uint32_t)mw, k + i);
+        const bool keep = !(__builtin_fabsf(x[i]) < th);
+        const uint64_t pb = __ballot(keep && x[i] > 0.0f) & m, nb = __ballot(keep && x[i] < 0.0f) & m;
+        p = lane == k + i ? pb : p;
+        n = lane == k + i ? nb : n;
+      }
+    }
+    if (valid) {
+      prow[k1 + lane] = p;
+      nrow[k1 + lane] = n;
+    }
+  }
+}
+
 // Count and decode (read side), as pass 2 with two counters: lane l counts
 // word k0 + l of the positive rows and of the negative rows; the planes of
 // both go through LDS so that each lane decodes four consecutive elements
@@ -252,7 +476,7 @@ __global__ __launch_bounds__(kThreads2) void k_tpass2(TernArgs a) {
     __syncthreads();
   }
   int64_t base, nbe, chunk0;
-  bucket_span(b, a.btab, a.n_total, a.bucket_n, 0, base, nbe, chunk0);
+  bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
   const int64_t nwords = (nbe + 63) / 64;
   const int64_t wbase = base / 64;
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront index, uniform
@@ -384,6 +608,18 @@ hipError_t launch_ternary_pack(const Geometry& geo, const TernArgs& a0, hipStrea
     }
   }
   return hipSuccess;
+}
+
+hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a, nf_worker_stats* win, hipStream_t s) {
+  hipLaunchKernelGGL(k_twindow, dim3((unsigned)geo.W, (unsigned)geo.nb), dim3(kThreads1), 0, s, a, win,
+                     geo.nb * geo.W >= 128 ? kSampleWords : kSampleWords / 4);
+  return hipGetLastError();
+}
+
+hipError_t launch_ternary_settle(const Geometry& geo, const TernArgs& a, hipStream_t s) {
+  const int64_t blocks = ceil_div((geo.max_len + 63) / 64, 4 * kThreads2);
+  hipLaunchKernelGGL(k_tsettle, dim3((unsigned)blocks, (unsigned)geo.nb, (unsigned)geo.W), dim3(kThreads2), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_ternary_reduce(const Geometry& geo, const TernArgs& a, hipStream_t s) {

@@ -1,0 +1,62 @@
+"""G-Ternary in one read, above the small problems: pass 1 packs by a window
+that a sample puts around each worker's threshold, the count settles what the
+window left open, and a worker whose threshold missed its window is packed
+anew.  Every output bit for bit against the oracle, by rows and by tiles, on
+data that makes the window good, poor, useless or wrong."""
+import numpy as np
+import pytest
+
+import oracle as nfo
+import paper_2606_25759_amd as nf
+import synth
+from tests.test_gpu_ternary import check_ternary_bucket, ternary_route
+
+pytestmark = pytest.mark.gpu
+
+BYTES = 640 << 20  # planes in one read above, and from eight workers
+# sizes just above it: eight workers by tiles, 24 by rows
+SIZES = [(8, BYTES // 32 + 77), (24, BYTES // 96 + 77)]
+
+
+def data(W, n, seed):
+    lay = synth.small(W, n, seed, elig_frac=0.85, nruns=17)
+    return synth.generate_host(lay), nfo.mask_from_segments(*synth.mask_segments(lay), n)
+
+
+@pytest.mark.parametrize("W,n", SIZES)
+@pytest.mark.parametrize("kind", ["normal", "tau0", "all_gated", "outliers", "sparse", "constant", "forced"])
+def test_windows(kind, W, n):
+    g, mask = data(W, n, n)
+    pol = nf.policy(format=nf.NF_FORMAT_TERNARY, tau={"tau0": 0.0, "all_gated": 1e30, "constant": 1.0}.get(kind, 0.5),
+                    force_lowbit=int(kind == "forced"))
+    rng = np.random.default_rng(1)
+    if kind == "outliers":
+        # a few huge elements between the sampled words move the mean
+        for w in range(3):
+            g[w, rng.choice(n, 40, replace=False)] = 3.0
+    elif kind == "sparse":
+        g[:, :n] *= rng.random((W, n), dtype=np.float32) < 1e-4
+        g[0, :n] = 0
+        g[0, n // 2: n // 2 + 5] = 1e-3
+    elif kind == "constant":
+        # |g| = theta = the mean everywhere: neither below the gate nor far from it
+        g[:, :n] = np.where(rng.random((W, n)) < 0.5, np.float32(-2.0 ** -9), np.float32(2.0 ** -9))
+    elif kind == "forced":
+        g[1, ::1001] = np.nan
+        g[2, 5::100_003] = np.inf
+    res = ternary_route(g, mask, n, pol)
+    route = check_ternary_bucket(res, g, mask, n, pol, 0, n, f"{kind} W={W}")
+    assert kind in ("sparse", "outliers") or route == nfo.ROUTE_L
+
+
+@pytest.mark.parametrize("W,n,bucket_n", [(17, 9_900_001, 3_000_000), (70, 2_400_001, 131_072), (66, 4_200_000, 2_000_000)])
+def test_windows_many_workers(W, n, bucket_n):
+    """Row groups, several buckets, one of them falling back, one all FP32."""
+    g, mask = data(W, n, W)
+    if bucket_n < n:
+        mask[:bucket_n // 64] = 0
+        g[W - 1, n - 1] = np.inf
+    pol = nf.policy(format=nf.NF_FORMAT_TERNARY, decode_mode=1)
+    res = ternary_route(g, mask, n, pol, bucket_n)
+    for b in range(-(-n // bucket_n)):
+        check_ternary_bucket(res, g, mask, n, pol, b, bucket_n, f"W={W} bucket {b}")
