@@ -62,15 +62,25 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   const int64_t tb = c * a.G;
   const int64_t te = (tb + a.G < ntiles) ? tb + a.G : ntiles;
   const bool stage_on = a.sums != kSumsNone;
-  // LDS: the chunk's sign words [W][G * EG * NW], then the FP32 stage [W][tile]
+  // LDS: the chunk's sign words [W][G * EG * NW] (or both planes'), then the
+  // FP32 stage [W][tile]
   const int cw = a.G * a.eg * NW;  // sign words per worker and chunk
   uint64_t* wbuf = reinterpret_cast<uint64_t*>(smem);
   uint64_t* nbuf = wbuf + (size_t)a.W * cw;  // TERN: the negative planes'
   const size_t stage_off = (PACK ? 1 : TERN ? 2 : 0) * (size_t)a.W * cw * sizeof(uint64_t);
   float* stage = reinterpret_cast<float*>(smem + stage_off);
+  // Without sign words the stage has two halves that tiles take in turn: a
+  // wavefront that writes a tile's half has passed the barrier of the tile
+  // before, hence all have read the tile before that.
+  constexpr int HALVES = PACK || TERN ? 1 : 2;
+  int spar = 0;  // the current half's first float
+  auto next_stage = [&]() {
+    if (HALVES == 2) spar = spar ? 0 : a.W * tile;
+    else __syncthreads();
+  };
   // then the chunk's mask words [G * EG * NW] (mixed chunks)
   uint64_t* mwords =
-      reinterpret_cast<uint64_t*>(smem + stage_off + (stage_on ? (size_t)a.W * tile * sizeof(float) : 0));
+      reinterpret_cast<uint64_t*>(smem + stage_off + (stage_on ? (size_t)HALVES * a.W * tile * sizeof(float) : 0));
   __shared__ uint32_t tflags;  // mixed chunks: bit i = tile tb + i has a routed element
   if (threadIdx.x == 0) tflags = 0;
   // FP32 sum at a position: an earlier row group's running sum comes first;
@@ -516,7 +526,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           if constexpr (!EXACT) sabs[j] += s1;
           ssq[j] += s2;
           if (stage_tile) {
-            float* st = stage + (int64_t)w * tile + eg * T + lane;
+            float* st = stage + spar + w * tile + eg * T + lane;
 #pragma unroll
             for (int k = 0; k < NW; ++k) st[64 * k] = x[k];
           }
@@ -531,12 +541,11 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           const uint64_t pick = a.sums == kSumsAll ? ~0ull : ~mwords[ti * nwt + kw];
           const int e = kw * 64 + lane;
           if ((pick >> lane) & 1ull) {
-            float s2 = sum_first(base + t0 + e, stage[e]);
-            for (int w = 1; w < a.W; ++w) s2 = s2 + stage[w * tile + e];
-            out[base + t0 + e] = sum_last(s2);
+            const float* st = stage + spar + e;
+            out[base + t0 + e] = sum_last(worker_sum(sum_first(base + t0 + e, *st), st + tile, tile, a.W - 1));
           }
         }
-        __syncthreads();
+        next_stage();
       }
     };
     int64_t t = tb;
@@ -689,7 +698,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if constexpr (!EXACT) sabs[j] += s1;
         ssq[j] += s2;
         if (stage_tile) {
-          float* st = stage + (int64_t)w * tile + eg * T + lane;
+          float* st = stage + spar + w * tile + eg * T + lane;
 #pragma unroll
           for (int k = 0; k < NW; ++k) st[64 * k] = x[k];
         }
@@ -705,12 +714,11 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         const int e = kw * 64 + lane;
         const uint64_t pick = (a.sums == kSumsAll ? ~0ull : ~tmask[kw]) & low_bits(lim - kw * 64);
         if ((pick >> lane) & 1ull) {
-          float s = sum_first(base + t0 + e, stage[e]);
-          for (int w = 1; w < a.W; ++w) s = s + stage[w * tile + e];
-          out[base + t0 + e] = sum_last(s);
+          const float* st = stage + spar + e;
+          out[base + t0 + e] = sum_last(worker_sum(sum_first(base + t0 + e, *st), st + tile, tile, a.W - 1));
         }
       }
-      __syncthreads();
+      next_stage();
     }
   }
 
@@ -961,7 +969,7 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
   const int R = geo.rows;  // workers of the largest row group
   const int cw = geo.G * geo.eg * pass1_words(geo.wpw);
   size_t smem = (PACK ? 1 : TERN ? 2 : 0) * (size_t)R * cw * sizeof(uint64_t);
-  if (a0.sums != kSumsNone) smem += (size_t)R * geo.tile * sizeof(float);
+  if (a0.sums != kSumsNone) smem += (size_t)(PACK || TERN ? 1 : 2) * R * geo.tile * sizeof(float);
   smem += (size_t)geo.G * geo.eg * pass1_words(geo.wpw) * sizeof(uint64_t);  // mask words of a mixed chunk
   size_t red = (size_t)geo.eg * R * sizeof(Partial) + (size_t)geo.eg * sizeof(uint64_t);
   // routed chunks with several workers per wavefront: [kWaves][W] partials
