@@ -61,7 +61,7 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a0, hipStream_t s) 
       a.win = a0.win + wb;
     }
     a.part = a0.part + wb;
-    a.parts = pass1_parts(rows);
+    a.parts = pass1_parts(rows, a.item_words / kBatch);
     // sign words: a row for each wavefront, or (several items a worker) for
     // each worker
     const size_t lds =
