@@ -186,6 +186,8 @@ nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stri
     a.bstride = tern->bstride;
     a.nbits = tern->bits + (int64_t)geo.W * tern->bstride;
     a.win = stats;
+    a.win0 = stats;
+    a.ratio = nf::plane_ratio(*pol);
     tern->part = a.part;
     tern->slots = geo.slots;
   }

@@ -42,6 +42,10 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
     float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, Pass1Args a,
     int64_t q0) {
   constexpr int NW = pass1_words(WPW);
+  // G-Ternary: look for the fallback ahead (see Window).  With four workers
+  // per wavefront the loops are out of registers: 14 spilled, and an ordinary
+  // step of 128 workers, 8 GB took 3.08 ms instead of 2.62.
+  constexpr bool LOOK = TERN && WPW < 4;
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t q = q0 + blockIdx.x;  // this block's chunk
   if (q >= a.total_chunks) return;     // whole block
@@ -53,6 +57,8 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront index, uniform
   const int lane = threadIdx.x & 63;
+  if (LOOK && c == 0 && v == kWaves - 1 && a.win == a.win0 && a.ratio >= 0.0f)
+    foretell(a.win0 + (int64_t)b * a.wtot, a.wtot, a.ratio);
   const int wg = v % a.wg;
   const int eg = v / a.wg;
   const bool active = eg < a.eg;
@@ -90,7 +96,9 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
 
   // G-Ternary: the windows of this wavefront's workers (see tern_words).
   float wlo[WPW], whi[WPW];
+  float ahead = 0.0f;
   if constexpr (TERN) {
+    if (LOOK) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
       const int w = wg + j * a.wg;
@@ -206,6 +214,10 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       consume(xa);
     }
   }
+
+  // G-Ternary: no planes in a bucket that falls back (see Window).  This load
+  // came in before the mask words did.
+  const bool drop = LOOK && __builtin_amdgcn_readfirstlane((int)(ahead != 0.0f)) != 0;
 
   // Chunks with every element routed to FP32, several workers per
   // wavefront: element-major like the one-worker case below, but the
@@ -417,7 +429,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         s1 += __builtin_fabs(d);
         if constexpr (EXACT) umt = term_umin(umt, x[k]);
       }
-      if constexpr (TERN) {
+      if (TERN && !drop) {
         uint64_t pb[NW], nb[NW];
 #pragma unroll
         for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], ~0ull, pb[k], nb[k]);
@@ -432,6 +444,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       if (__ballot(!finite64(s2))) {
 #pragma unroll
         for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
+        if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
       }
       if constexpr (!EXACT) sabs[j] += s1;
       ssq[j] += s2;
@@ -502,7 +515,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
             s1 += el ? __builtin_fabs(d) : 0.0;
             if constexpr (EXACT) umt = term_umin(umt, el ? x[k] : 0.0f);
           }
-          if constexpr (TERN) {
+          if (TERN && !drop) {
             uint64_t pb[NW], nb[NW];
 #pragma unroll
             for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
@@ -522,6 +535,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           if (__ballot(!finite64(s2))) {
 #pragma unroll
             for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
+            if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
           }
           if constexpr (!EXACT) sabs[j] += s1;
           ssq[j] += s2;
@@ -672,7 +686,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
             if constexpr (EXACT) umt = term_umin(umt, el ? x[k] : 0.0f);
           }
         }
-        if constexpr (TERN) {
+        if (TERN && !drop) {
           uint64_t pb[NW], nb[NW];
 #pragma unroll
           for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
@@ -694,6 +708,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if (__ballot(!finite64(s2))) {
 #pragma unroll
           for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
+          if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
         }
         if constexpr (!EXACT) sabs[j] += s1;
         ssq[j] += s2;
@@ -741,7 +756,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       if (w >= a.W) break;
       if (PACK)
         for (int o = lane; o < valid; o += 64) bits[(int64_t)w * a.bstride + gw0 + o] = wbuf[w * cw + o];
-      if (TERN)
+      if (TERN && !drop)
         for (int o = lane; o < valid; o += 64) {
           bits[(int64_t)w * a.bstride + gw0 + o] = wbuf[w * cw + o];
           a.nbits[(int64_t)w * a.bstride + gw0 + o] = nbuf[w * cw + o];
@@ -764,7 +779,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
 
   __syncthreads();
   // The chunk's sign words, row by row, as coalesced stores.
-  if ((PACK || TERN) && te > tb) {
+  if ((PACK || (TERN && !drop)) && te > tb) {
     const int64_t e_beg = tb * tile;
     const int64_t e_end = (te * tile < nbe) ? te * tile : nbe;
     const int valid = (int)((e_end - e_beg + 63) / 64);
@@ -940,16 +955,19 @@ __global__ __launch_bounds__(kDecideThreads) void k_decide(DecideArgs a) {
     if (lane == 0) ne_s = s;
   }
   __syncthreads();
+  // G-Ternary: the planes are whole unless some block saw the fallback ahead.
+  const bool dropped = a.windows && load_ahead(a.stats + (int64_t)b * a.W) != 0.0f;
   uint32_t resummed = 0;
-  if (EXACT) resummed = resum_exact(st, redo, a, base, nbe, hist);
+  if (EXACT) resummed = resum_exact(st, redo, a, base, nbe, hist);  // ends with a barrier
   for (int w = threadIdx.x; w < a.W; w += kDecideThreads) {
     if (a.windows) {
-      // G-Ternary: did the worker's threshold fall into the window that pass
-      // 1 packed its planes by?  The answer takes a dead field of its first
-      // partial.
+      // G-Ternary: did pass 1 store the planes, and did the worker's
+      // threshold fall into the window that they are packed by?  The answer
+      // takes a dead field of its first partial.
       const Window wd = load_window(a.stats, (int64_t)b * a.W + w);
       const float theta = ternary_threshold(st[w], (int64_t)ne_s, a.pol.tau);
-      const_cast<Partial*>(a.part)[chunk0 * a.W + w].sabs_b = (wd.lo <= theta && theta <= wd.hi) ? 0.0 : 1.0;
+      const_cast<Partial*>(a.part)[chunk0 * a.W + w].sabs_b =
+          (!dropped && wd.lo <= theta && theta <= wd.hi) ? 0.0 : 1.0;
     }
     a.stats[(int64_t)b * a.W + w] = st[w];
   }

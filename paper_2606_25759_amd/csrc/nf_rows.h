@@ -43,8 +43,13 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
   // FP32 sums at a position: an earlier row group's running sum comes first;
   // the mean divides by all workers after the last group.
   auto sum_last = [&](float s) { return a.mean && a.rfin ? s / (float)a.wtot : s; };
+  // G-Ternary: no planes in a bucket that falls back (see Window); waited for
+  // once the first gradients are on their way.
+  float ahead = 0.0f;
+  if (TERN) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
   // Worker w's sign words, whole in LDS, to memory by one wavefront.
   auto put_row = [&](int w, const uint64_t* words) {
+    if (TERN && ahead != 0.0f) return;
     uint64_t* to = a.bits + (int64_t)w * a.bstride + e0 / 64;
     for (int i = lane; i < nwc; i += 64) to[i] = words[i];
     if (TERN) {
@@ -77,12 +82,13 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
       double s1 = 0.0, s2 = 0.0;
       uint32_t umt = ~0u, el8 = 0;
       uint64_t bb[NW], nb[NW];
+      const bool skip = TERN && __builtin_amdgcn_readfirstlane((int)(ahead != 0.0f)) != 0;
 #pragma unroll
       for (int u = 0; u < NW; ++u) {
         const uint64_t m = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(mv >> 32), u) << 32) |
                            (uint32_t)__builtin_amdgcn_readlane((uint32_t)mv, u);
         if (PACK) bb[u] = __ballot(x[u] > 0.0f) & m;
-        if (TERN) tern_words(x[u], wd.lo, wd.hi, m, bb[u], nb[u]);
+        if (TERN && !skip) tern_words(x[u], wd.lo, wd.hi, m, bb[u], nb[u]);
         const bool el = __builtin_amdgcn_inverse_ballot_w64(m);
         const double d = (double)x[u];
         s2 = __builtin_fma(d, d, s2);
@@ -98,9 +104,10 @@ __device__ __forceinline__ void chunk_by_rows(const Pass1Args& a, int64_t q, int
       if (__ballot(!finite64(s2))) {
 #pragma unroll
         for (int u = 0; u < NW; ++u) nonf += __popcll(__ballot(!finite32(x[u])));
+        if (TERN && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
       }
       if (w == 0 && lane < NW) ne += __popcll(mv);
-      if (PACK || TERN) {
+      if (PACK || (TERN && !skip)) {
         uint32_t lo, hi;
         lanes_from_ballots<NW>(bb, lo, hi);
         if (lane < NW) words[k + lane] = ((uint64_t)hi << 32) | lo;

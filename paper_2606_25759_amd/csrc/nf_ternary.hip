@@ -28,7 +28,7 @@ namespace nf {
 // costs a second read of that worker's rows, not a result.
 __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_stats* win, int most) {
   __shared__ double r1[kWaves], r2[kWaves];
-  __shared__ uint32_t rn[kWaves];
+  __shared__ uint32_t rn[kWaves], rbad[kWaves];
   const int w = blockIdx.x, b = blockIdx.y;
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -45,7 +45,8 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
   }
   double s1 = 0.0, s2 = 0.0;
   uint32_t n = 0;
-  constexpr int NL = 16;  // words in flight
+  bool bad = false;
+  constexpr int NL = 32;  // words in flight
 #pragma unroll 1
   for (int64_t j0 = v * 64; j0 < ns; j0 += kThreads1) {
     // this lane's sampled word, from stretch j of ns, and its mask word
@@ -61,6 +62,7 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
 #pragma unroll 1
     for (int i = 0; i < mine; i += NL) {
       float x[NL];
+      float f1 = 0.0f, f2 = 0.0f;  // FP32 will do for the window (all in FP64 took half the kernel's time)
 #pragma unroll
       for (int u = 0; u < NL; ++u) {
         const int64_t e = 64 * (int64_t)__builtin_amdgcn_readlane((int)k, i + u) + lane;
@@ -70,11 +72,14 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
       for (int u = 0; u < NL; ++u) {
         const uint64_t mu = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(m >> 32), i + u) << 32) |
                             (uint32_t)__builtin_amdgcn_readlane((uint32_t)m, i + u);
-        const bool el = __builtin_amdgcn_inverse_ballot_w64(mu) && finite32(x[u]);
-        const double d = el ? (double)x[u] : 0.0;
-        s1 += __builtin_fabs(d);
-        s2 = __builtin_fma(d, d, s2);
+        const bool fin = finite32(x[u]);
+        bad |= !fin;
+        const float d = __builtin_amdgcn_inverse_ballot_w64(mu) && fin ? x[u] : 0.0f;
+        f1 += __builtin_fabsf(d);
+        f2 = __builtin_fmaf(d, d, f2);
       }
+      s1 += (double)f1;
+      s2 += (double)f2;
     }
   }
   s1 = wave_sum(s1);
@@ -85,10 +90,13 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
     r2[v] = s2;
     rn[v] = n;
   }
+  if (const uint64_t any = __ballot(bad); lane == 0) rbad[v] = any != 0;
   __syncthreads();
   if (threadIdx.x == 0) {
     double t1 = 0.0, t2 = 0.0, tn = 0.0;
+    uint32_t some_bad = 0;
     for (int i = 0; i < kWaves; ++i) {
+      some_bad |= rbad[i];
       t1 += r1[i];
       t2 += r2[i];
       tn += (double)rn[i];
@@ -103,6 +111,8 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
     float* f = reinterpret_cast<float*>(win + (int64_t)b * a.W + w);
     f[0] = (float)(theta * (1.0 - eps));
     f[1] = (float)(theta * (1.0 + eps));
+    f[2] = t1 > 0.0 && !some_bad ? (float)(t2 / tn) : -1.0f;
+    f[3] = 0.0f;
   }
 }
 

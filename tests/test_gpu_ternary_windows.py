@@ -1,7 +1,7 @@
 """G-Ternary in one read, above the small problems: pass 1 packs by a window
 that a sample puts around each worker's threshold, the count settles what the
 window left open, and a worker whose threshold missed its window is packed
-anew.  Every output bit for bit against the oracle, by rows and by tiles, on
+anew, as is a bucket whose foretold fallback does not come.  Every output bit for bit against the oracle, by rows and by tiles, on
 data that makes the window good, poor, useless or wrong."""
 import numpy as np
 import pytest
@@ -24,7 +24,8 @@ def data(W, n, seed):
 
 
 @pytest.mark.parametrize("W,n", SIZES)
-@pytest.mark.parametrize("kind", ["normal", "tau0", "all_gated", "outliers", "sparse", "constant", "forced"])
+@pytest.mark.parametrize("kind", ["normal", "tau0", "all_gated", "outliers", "sparse", "constant", "forced",
+                                  "overflow", "spike", "false_spike"])
 def test_windows(kind, W, n):
     g, mask = data(W, n, n)
     pol = nf.policy(format=nf.NF_FORMAT_TERNARY, tau={"tau0": 0.0, "all_gated": 1e30, "constant": 1.0}.get(kind, 0.5),
@@ -44,9 +45,23 @@ def test_windows(kind, W, n):
     elif kind == "forced":
         g[1, ::1001] = np.nan
         g[2, 5::100_003] = np.inf
+    elif kind == "overflow":
+        # found while pass 1 reads, which then stores no more planes
+        g[W // 3, rng.choice(n, 40, replace=False)] = np.inf
+    elif kind == "spike":
+        g[W // 2] *= 10
+    elif kind == "false_spike":
+        # a spike of the eligible elements, foretold by the sample, drowns in the routed ones: no planes from pass 1,
+        # yet the low-bit route
+        el = np.unpackbits(mask.view(np.uint8), bitorder="little")[:n].astype(bool)
+        g[W // 2, :n][el] *= 10
+        g[:, :n][:, ~el] *= 1e4
     res = ternary_route(g, mask, n, pol)
     route = check_ternary_bucket(res, g, mask, n, pol, 0, n, f"{kind} W={W}")
-    assert kind in ("sparse", "outliers") or route == nfo.ROUTE_L
+    if kind in ("overflow", "spike"):
+        assert route == nfo.ROUTE_F
+    else:
+        assert kind in ("sparse", "outliers") or route == nfo.ROUTE_L
 
 
 @pytest.mark.parametrize("W,n,bucket_n", [(17, 9_900_001, 3_000_000), (70, 2_400_001, 131_072), (66, 4_200_000, 2_000_000)])
