@@ -94,11 +94,14 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   auto sum_first = [&](int64_t pos, float x0) { return a.racc ? out[pos] + x0 : x0; };
   auto sum_last = [&](float s) { return a.mean && a.rfin ? s / (float)a.wtot : s; };
 
-  // G-Ternary: the windows of this wavefront's workers (see tern_words).
+  // G-Ternary: the windows of this wavefront's workers (see tern_words).  The
+  // bucket's flag is read once for the block: other blocks set it meanwhile,
+  // and what hangs on it has a block barrier inside.
   float wlo[WPW], whi[WPW];
+  __shared__ uint32_t ahead_s;
   float ahead = 0.0f;
   if constexpr (TERN) {
-    if (LOOK) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
+    if (LOOK && threadIdx.x == 0) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
       const int w = wg + j * a.wg;
@@ -184,6 +187,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       m0 = mask[wbeg + ((int)threadIdx.x < nwc ? (int)threadIdx.x : nwc - 1)];
       issue_words(tb, xa);
     }
+    if (LOOK && threadIdx.x == 0) ahead_s = ahead != 0.0f;  // came in before m0
     const bool mine = (int)threadIdx.x < nwc;
     int some_not = !all_full || (mine && m0 != ~0ull);
     int some_set = !all_full || (mine && m0 != 0ull);
@@ -215,9 +219,9 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
     }
   }
 
-  // G-Ternary: no planes in a bucket that falls back (see Window).  This load
-  // came in before the mask words did.
-  const bool drop = LOOK && __builtin_amdgcn_readfirstlane((int)(ahead != 0.0f)) != 0;
+  // G-Ternary: no planes in a bucket that falls back (see Window), the same in
+  // all wavefronts of the block.
+  const bool drop = LOOK && __builtin_amdgcn_readfirstlane((int)ahead_s) != 0;
 
   // Chunks with every element routed to FP32, several workers per
   // wavefront: element-major like the one-worker case below, but the
