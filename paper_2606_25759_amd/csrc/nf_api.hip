@@ -180,16 +180,16 @@ nf_status run_pass1_decide(const nf::Geometry& geo, const float* g, int64_t stri
   if (tern) {
     // G-Ternary in one read: the windows first (in stats until the decision
     // writes it), then pass 1 with both planes.
-    e = nf::launch_ternary_window(geo, *tern, stats, s);
+    tern->part = a.part;
+    tern->slots = geo.slots;
+    a.ratio = nf::plane_ratio(*pol);
+    e = nf::launch_ternary_window(geo, *tern, a.part, stats, a.ratio, s);
     if (e != hipSuccess) return hip_fail(e, "ternary window launch");
     a.bits = tern->bits;
     a.bstride = tern->bstride;
     a.nbits = tern->bits + (int64_t)geo.W * tern->bstride;
     a.win = stats;
     a.win0 = stats;
-    a.ratio = nf::plane_ratio(*pol);
-    tern->part = a.part;
-    tern->slots = geo.slots;
   }
   e = nf::launch_pass1(geo, a, s);
   if (e != hipSuccess) return hip_fail(e, "pass-1 launch");

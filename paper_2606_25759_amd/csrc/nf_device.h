@@ -413,40 +413,14 @@ __device__ __forceinline__ Window load_window(const nf_worker_stats* win, int64_
 }
 
 // A bucket's `ahead` (see Window), in its first worker's window.  Pass 1's
-// blocks set and read it across XCDs while it runs, hence the agent scope.
+// blocks set it while others read it.  The load may come from the XCD's own L2
+// and be some microseconds old, which costs a chunk's planes and no result;
+// past the L2s it held up every chunk's first barrier.
 __device__ __forceinline__ float load_ahead(const nf_worker_stats* win) {
-  return __hip_atomic_load(reinterpret_cast<const float*>(win) + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __hip_atomic_load(reinterpret_cast<const float*>(win) + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ void set_ahead(nf_worker_stats* win) {
   __hip_atomic_store(reinterpret_cast<float*>(win) + 3, 1.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// One wavefront: does the sample foretell the fallback?
-__device__ __forceinline__ void foretell(nf_worker_stats* win, int W, float ratio) {
-  const int lane = threadIdx.x & 63;
-  uint32_t most = 0;  // powers as bits: from 0 on they are ordered alike
-  bool bad = false;
-#pragma unroll 1
-  for (int w = lane; w < W; w += 64) {
-    const float x = reinterpret_cast<const float*>(win + w)[2];
-    bad |= x < 0.0f;
-    const uint32_t u = __float_as_uint(x);
-    most = x >= 0.0f && u > most ? u : most;
-  }
-  group_steps(64, [&](auto step) {
-    const uint32_t y = step.of(most);
-    most = y > most ? y : most;
-  });
-  const float top = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)most, 63));
-  // the largest above `ratio` times the lower median: more than half of the
-  // workers are that far below it
-  int below = 0;
-#pragma unroll 1
-  for (int w0 = 0; w0 < W; w0 += 64) {
-    const int w = w0 + lane;
-    below += __popcll(__ballot(w < W && ratio * reinterpret_cast<const float*>(win + (w < W ? w : 0))[2] < top));
-  }
-  const bool ahead = __ballot(bad) != 0 || below > (W - 1) / 2;
-  if (ahead && lane == 0) set_ahead(win);
 }
 
 // One element a lane into a word of both planes, m the word's mask: kept and

@@ -450,14 +450,14 @@ enum Pass2Op { kOpCountDecode = 0, kOpFp32 = 1, kOpFromDecision = 2, kOpFallback
 // elements are read again and their words corrected.  The windows wait in
 // the first 16 bytes of the bucket's statistics, until the decision.
 //
-// A bucket that falls back needs no planes, and a step would pay for them (a
-// fallback of 16 workers, 8 GB: 3.0 ms without, 3.5 with).  power is the
-// sample's mean g*g, or -1 for a worker whose sample is all zeros or holds a
-// non-finite value; ahead (in the first worker's window) turns 1 in pass 1's
-// first chunk of the bucket if there is a -1 or the norms of the sample
-// differ by sqrt(2) kappa, and wherever pass 1 meets a non-finite value.
-// Chunks that start later pack no planes.  Should the bucket take the low-bit
-// route all the same, all its rows are packed anew.
+// A bucket that falls back needs no planes, and a step would pay for them (16
+// workers, 8 GB: pass 1 1.5 ms without, 1.9 with).  power is the sample's mean
+// g*g, or -1 for a worker whose sample is all zeros or holds a non-finite
+// value; ahead (in the first worker's window) is 1 if there is a -1 or the
+// norms of the sample differ by sqrt(2) kappa, and then pass 1 packs nothing
+// of the bucket.  Up to 64 workers it also turns 1 wherever pass 1 meets a
+// non-finite value: chunks that start later pack no planes.  Should the
+// bucket take the low-bit route all the same, all its rows are packed anew.
 struct Window {
   float lo, hi, power, ahead;
 };
@@ -465,9 +465,28 @@ inline NF_HD float plane_ratio(const nf_route_policy& p) {
   return p.force_lowbit ? -1.0f : (float)(2.0 * p.kappa * p.kappa);  // negative: nothing is foretold
 }
 static_assert(sizeof(nf_worker_stats) >= sizeof(Window), "a window per worker");
-// Words of a bucket that a worker's sample reads at most (a quarter of them
-// where few blocks take samples, each a chain of reads).
+// Words of a bucket that a worker's sample reads at most, and those that a
+// block takes at a time.
 constexpr int kSampleWords = 4096;
+constexpr int kSampleBlock = 512;
+// The words sampled of a bucket of nw: 4%, 64 to `most`.  Of few blocks'
+// samples (most below kSampleWords) a large bucket's window is worth more.
+inline NF_HD int64_t sample_words(int64_t nw, int most) {
+  int64_t ns = nw <= 64 ? nw : nw / 24;
+  if (nw > 64 && ns < 64) ns = 64;
+  if (ns > most) {
+    const int64_t more = most < kSampleWords ? nw / 64 : 0;
+    ns = more > most ? (more < 4 * kSampleWords ? more : 4 * kSampleWords) : most;
+  }
+  return ns;
+}
+// Blocks that share them, at most one for each of the bucket's chunks (whose
+// partials hold what the blocks find).
+inline NF_HD int sample_parts(int64_t len, int most, int chunk) {
+  const int64_t parts = (sample_words((len + 63) / 64, most) + kSampleBlock - 1) / kSampleBlock;
+  const int64_t chunks = (len + chunk - 1) / chunk;
+  return (int)(parts < chunks ? parts : chunks);
+}
 
 // G-Ternary pack and count/decode.  Route-driven (dec != NULL): only the
 // buckets routed L, thresholds from stats and tau.  Standalone: one bucket,
@@ -482,7 +501,7 @@ struct TernArgs {
   const nf_worker_stats* stats;  // [bucket][W]
   const float* theta;
   const Partial* part;  // route-driven count: sabs_b of a worker's first partial is 1 if its window missed
-  int32_t slots;
+  int32_t slots, chunk;  // chunk: elements
   const float* scale;
   uint8_t* cpos;  // nullable
   uint8_t* cneg;  // nullable
@@ -707,7 +726,8 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a, hipStream_t s);
 hipError_t launch_small2(const Geometry& geo, const Small2Args& a, hipStream_t s);
 hipError_t launch_decide(const Geometry& geo, const DecideArgs& a, hipStream_t s);
 hipError_t launch_pass2(const Geometry& geo, const Pass2Args& a, hipStream_t s);
-hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a, nf_worker_stats* win, hipStream_t s);
+hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a, Partial* sample, nf_worker_stats* win,
+                                 float ratio, hipStream_t s);
 hipError_t launch_ternary_settle(const Geometry& geo, const TernArgs& a, hipStream_t s);
 hipError_t launch_ternary_pack(const Geometry& geo, const TernArgs& a, hipStream_t s);
 hipError_t launch_ternary_reduce(const Geometry& geo, const TernArgs& a, hipStream_t s);

@@ -31,25 +31,15 @@ namespace nf {
 // each) per worker and tile.  Lane l of a wavefront loads element 64k + l of
 // word k, so every load instruction reads 256 contiguous bytes and the ballot
 // of "g > 0" over the wavefront is exactly bitmap word k.  A block takes one
-// chunk (G tiles of one bucket); launch q0 takes chunks q0 .. q0 + grid - 1.
-// Occupancy: eight wavefronts per SIMD (64 VGPRs) for one or two workers
-// per wavefront with sign words; four without (the exact |g| sums need a few
-// registers more, and at 64 they spilled: G-Ternary's first pass at GPT
-// scale 23.2 ms against 13.6 ms at four) or with more workers.
-template <int WPW, bool PACK, bool TERN>
-__global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <= 2 && PACK ? 8 : 4, WPW <= 2 && PACK ? 8 : 4))) void k_pass1(
+// chunk q (G tiles of one bucket).  LOOK: G-Ternary planes unless the bucket's
+// flag says that it falls back.
+template <int WPW, bool PACK, bool TERN, bool LOOK>
+__device__ __forceinline__ void pass1_chunk(
     const float* __restrict__ g, const uint64_t* __restrict__ mask, uint64_t* __restrict__ bits,
-    float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, Pass1Args a,
-    int64_t q0) {
+    float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, const Pass1Args& a,
+    int64_t q) {
   constexpr int NW = pass1_words(WPW);
-  // G-Ternary: look for the fallback ahead (see Window).  With four workers
-  // per wavefront the loops are out of registers: 14 spilled, and an ordinary
-  // step of 128 workers, 8 GB took 3.08 ms instead of 2.62.
-  constexpr bool LOOK = TERN && WPW < 4;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int64_t q = q0 + blockIdx.x;  // this block's chunk
-  if (q >= a.total_chunks) return;     // whole block
-
   // chunk q -> bucket b, chunk c within it; the chunk's partials go to slot q
   int b;
   int64_t c, base, nbe, chunk0;
@@ -57,8 +47,6 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wavefront index, uniform
   const int lane = threadIdx.x & 63;
-  if (LOOK && c == 0 && v == kWaves - 1 && a.win == a.win0 && a.ratio >= 0.0f)
-    foretell(a.win0 + (int64_t)b * a.wtot, a.wtot, a.ratio);
   const int wg = v % a.wg;
   const int eg = v / a.wg;
   const bool active = eg < a.eg;
@@ -94,20 +82,23 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   auto sum_first = [&](int64_t pos, float x0) { return a.racc ? out[pos] + x0 : x0; };
   auto sum_last = [&](float s) { return a.mean && a.rfin ? s / (float)a.wtot : s; };
 
-  // G-Ternary: the windows of this wavefront's workers (see tern_words).  The
-  // bucket's flag is read once for the block: other blocks set it meanwhile,
-  // and what hangs on it has a block barrier inside.
-  float wlo[WPW], whi[WPW];
+  // G-Ternary: the workers' windows (see tern_words).  LOOK: they wait in LDS,
+  // and so does the bucket's flag (see Window), read once for the block: other
+  // blocks set it meanwhile, and what hangs on it has a block barrier inside.
+  __shared__ float2 win_s[LOOK ? kRowGroup : 1];
   __shared__ uint32_t ahead_s;
+  Window wd0{};
   float ahead = 0.0f;
-  if constexpr (TERN) {
-    if (LOOK && threadIdx.x == 0) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
+  float2 wdr[WPW];
+  if constexpr (LOOK) {
+    if ((int)threadIdx.x < a.W) wd0 = load_window(a.win, (int64_t)b * a.wtot + threadIdx.x);
+    if (threadIdx.x == 0) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
+  } else if constexpr (TERN) {
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
       const int w = wg + j * a.wg;
       const Window wd = load_window(a.win, (int64_t)b * a.wtot + (w < a.W ? w : wg));
-      wlo[j] = wd.lo;
-      whi[j] = wd.hi;
+      wdr[j] = float2{wd.lo, wd.hi};
     }
   }
   // Word k of this lane's NW of worker w's planes from word `at` of the chunk on.
@@ -187,7 +178,9 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       m0 = mask[wbeg + ((int)threadIdx.x < nwc ? (int)threadIdx.x : nwc - 1)];
       issue_words(tb, xa);
     }
-    if (LOOK && threadIdx.x == 0) ahead_s = ahead != 0.0f;  // came in before m0
+    // came in before m0
+    if (LOOK && (int)threadIdx.x < a.W) win_s[threadIdx.x] = float2{wd0.lo, wd0.hi};
+    if (LOOK && threadIdx.x == 0) ahead_s = ahead != 0.0f;
     const bool mine = (int)threadIdx.x < nwc;
     int some_not = !all_full || (mine && m0 != ~0ull);
     int some_set = !all_full || (mine && m0 != 0ull);
@@ -315,7 +308,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if (st >= nsteps) break;
         out[c0 + (int64_t)st * 64 + lane] = sum_last(run[i]);
       }
-      if (PACK || TERN) {
+      if (PACK || (TERN && !drop)) {
         const int64_t gw0 = c0 / 64;
         for (int i = threadIdx.x; i < a.W * nsteps; i += kThreads1) {
           const int w = i / nsteps;
@@ -368,7 +361,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       }
     }
     // Zero sign words for the chunk, row by row.
-    if (PACK || TERN) {
+    if (PACK || (TERN && !drop)) {
       const int64_t gw0 = c0 / 64;
       for (int i = threadIdx.x; i < a.W * nsteps; i += kThreads1) {
         const int w = i / nsteps;
@@ -423,6 +416,8 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         continue;
       }
       double s1 = 0.0, s2 = 0.0;
+      float2 wd{};
+      if (TERN) wd = LOOK ? win_s[w] : wdr[j];
       uint32_t umt = ~0u;
       uint64_t bb[NW];
 #pragma unroll
@@ -436,7 +431,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       if (TERN && !drop) {
         uint64_t pb[NW], nb[NW];
 #pragma unroll
-        for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], ~0ull, pb[k], nb[k]);
+        for (int k = 0; k < NW; ++k) tern_words(x[k], wd.x, wd.y, ~0ull, pb[k], nb[k]);
         put_planes(w, (ti * a.eg + eg) * NW, pb, nb, NW);
       }
       if constexpr (EXACT) tile_into_lane<NW>(sabs[j], sabc[j], snz[j], um[j], tw[j], s1, umt, rp[j] + t * tile, ~0u);
@@ -448,7 +443,6 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       if (__ballot(!finite64(s2))) {
 #pragma unroll
         for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
-        if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
       }
       if constexpr (!EXACT) sabs[j] += s1;
       ssq[j] += s2;
@@ -508,6 +502,8 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
             continue;
           }
           double s1 = 0.0, s2 = 0.0;
+          float2 wd{};
+          if (TERN) wd = LOOK ? win_s[w] : wdr[j];
           uint32_t umt = ~0u;
           uint64_t bb[NW];
 #pragma unroll
@@ -522,7 +518,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           if (TERN && !drop) {
             uint64_t pb[NW], nb[NW];
 #pragma unroll
-            for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
+            for (int k = 0; k < NW; ++k) tern_words(x[k], wd.x, wd.y, mw[k], pb[k], nb[k]);
             put_planes(w, (ti * a.eg + eg) * NW, pb, nb, NW);
           }
           if constexpr (EXACT) {
@@ -539,7 +535,6 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           if (__ballot(!finite64(s2))) {
 #pragma unroll
             for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
-            if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
           }
           if constexpr (!EXACT) sabs[j] += s1;
           ssq[j] += s2;
@@ -668,6 +663,8 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
           }
         }
         double s1 = 0.0, s2 = 0.0;
+        float2 wd{};
+        if (TERN) wd = LOOK ? win_s[w] : wdr[j];
         uint32_t umt = ~0u;
         uint64_t bb[NW];
         if (mine_all) {
@@ -693,7 +690,7 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if (TERN && !drop) {
           uint64_t pb[NW], nb[NW];
 #pragma unroll
-          for (int k = 0; k < NW; ++k) tern_words(x[k], wlo[j], whi[j], mw[k], pb[k], nb[k]);
+          for (int k = 0; k < NW; ++k) tern_words(x[k], wd.x, wd.y, mw[k], pb[k], nb[k]);
           put_planes(w, (int)((t - tb) * a.eg + eg) * NW, pb, nb, nwv < NW ? nwv : NW);
         }
         if constexpr (EXACT) {
@@ -712,7 +709,6 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
         if (__ballot(!finite64(s2))) {
 #pragma unroll
           for (int k = 0; k < NW; ++k) nonf[j] += __popcll(__ballot(!finite32(x[k])));
-          if (LOOK && lane == 0 && a.ratio >= 0.0f) set_ahead(a.win0 + (int64_t)b * a.wtot);
         }
         if constexpr (!EXACT) sabs[j] += s1;
         ssq[j] += s2;
@@ -739,6 +735,14 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
       }
       next_stage();
     }
+  }
+
+  // the chunks that start from now on (see Window)
+  if (LOOK && a.ratio >= 0.0f) {
+    uint64_t some = 0;
+#pragma unroll
+    for (int j = 0; j < WPW; ++j) some |= nonf[j];
+    if (some && lane == 0) set_ahead(a.win0 + (int64_t)b * a.wtot);
   }
 
   const int64_t slot = q;  // the chunk's own partial slot
@@ -830,6 +834,38 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
     uint64_t s = 0;
     for (int e = 0; e < a.eg; ++e) s += red_ne[e];
     part_ne[slot] = s;
+  }
+}
+
+// Launch q0 takes chunks q0 .. q0 + grid - 1.
+// Occupancy: eight wavefronts per SIMD (64 VGPRs) for one or two workers
+// per wavefront with sign words; four without (the exact |g| sums need a few
+// registers more, and at 64 they spilled: G-Ternary's first pass at GPT
+// scale 23.2 ms against 13.6 ms at four) or with more workers.
+// G-Ternary with four workers per wavefront: the loops have no register left
+// for the flag (14 spilled, and an ordinary step of 128 workers, 8 GB took
+// 3.08 ms instead of 2.62; with the windows in LDS none, but 2.71), so a block
+// runs one of two codes by what the sample foretold.  That does not change
+// while pass 1 runs, so every wavefront reads the same.  A fallback of 128
+// workers, 8 GB takes 2.90 ms (3.53 with planes packed all the same, 2.86 with
+// two reads), an ordinary step 2.67 (2.65 without the choice).
+template <int WPW, bool PACK, bool TERN>
+__global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <= 2 && PACK ? 8 : 4, WPW <= 2 && PACK ? 8 : 4))) void k_pass1(
+    const float* __restrict__ g, const uint64_t* __restrict__ mask, uint64_t* __restrict__ bits,
+    float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, Pass1Args a,
+    int64_t q0) {
+  const int64_t q = q0 + blockIdx.x;  // this block's chunk
+  if (q >= a.total_chunks) return;     // whole block
+  if constexpr (TERN && WPW == 4) {
+    int b;
+    int64_t c;
+    chunk_home(q, a.btab, a.cbucket, a.nb, a.chunks_full, b, c);
+    if (uniform32((int)(load_window(a.win0, (int64_t)b * a.wtot).ahead != 0.0f)))
+      pass1_chunk<WPW, false, false, false>(g, mask, bits, out, part, part_ne, a, q);
+    else
+      pass1_chunk<WPW, false, true, false>(g, mask, bits, out, part, part_ne, a, q);
+  } else {
+    pass1_chunk<WPW, PACK, TERN, TERN>(g, mask, bits, out, part, part_ne, a, q);
   }
 }
 
@@ -991,7 +1027,9 @@ static hipError_t pass1_dispatch(const Geometry& geo, const Pass1Args& a0, hipSt
   const int R = geo.rows;  // workers of the largest row group
   const int cw = geo.G * geo.eg * pass1_words(geo.wpw);
   size_t smem = (PACK ? 1 : TERN ? 2 : 0) * (size_t)R * cw * sizeof(uint64_t);
-  if (a0.sums != kSumsNone) smem += (size_t)(PACK || TERN ? 1 : 2) * R * geo.tile * sizeof(float);
+  const size_t stage = a0.sums != kSumsNone ? (size_t)R * geo.tile * sizeof(float) : 0;
+  smem += (PACK || TERN ? 1 : 2) * stage;
+  if (TERN && smem < 2 * stage) smem = 2 * stage;  // chunks that pack no planes
   smem += (size_t)geo.G * geo.eg * pass1_words(geo.wpw) * sizeof(uint64_t);  // mask words of a mixed chunk
   size_t red = (size_t)geo.eg * R * sizeof(Partial) + (size_t)geo.eg * sizeof(uint64_t);
   // routed chunks with several workers per wavefront: [kWaves][W] partials

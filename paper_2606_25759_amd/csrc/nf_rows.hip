@@ -21,8 +21,6 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(PACK 
   const int64_t ch = (int64_t)a.G * a.eg * a.T;  // elements of a whole chunk
   const int64_t e0 = base + c * ch;
   const int len = (int)(nbe - c * ch < ch ? nbe - c * ch : ch);  // >= 1
-  if (TERN && c == 0 && threadIdx.x < 64 && a.win == a.win0 && a.ratio >= 0.0f)
-    foretell(a.win0 + (int64_t)b * a.wtot, a.wtot, a.ratio);
   chunk_by_rows<PACK, TERN, SMALL, CACHED>(a, q, b, e0, len, lds, red, red_ne);
 }
 

@@ -1,7 +1,8 @@
 // nf_ternary.hip - G-Ternary write side and count/decode (§2.2; gfx950).
 //
-//   k_twindow a sample of every bucket and worker: the window around its
-//             threshold by which pass 1 packs the planes as it reads
+//   k_tsample a sample of every bucket and worker
+//   k_twindow the window around each worker's threshold by which pass 1 packs
+//             the planes as it reads
 //   k_tsettle the elements that the window left open, read again
 //   k_tpack   both planes per worker from given thresholds, laid out as
 //             pass 1's chunks: in a second read of the gradients, or from
@@ -16,71 +17,66 @@ namespace nf {
 
 // ------------------------------------------------------- threshold windows
 //
-// Block (worker, bucket): the mean |g| of a sample of the worker's eligible
-// elements, at most `most` words, one from each of as many stretches of
-// the bucket (so that every parameter's scale is met), at a place of its own
-// in each.  The threshold is tau times the whole bucket's mean; with S1 and
-// S2 the sample's sums of |g| and g*g, a mean over independent elements is
-// off by less than sqrt(S2) / S1 of itself (one deviation; for normal values
-// 1.25 / sqrt(m), and truly 0.75 / sqrt(m)), and the window is two of these
-// wide on either side: about 0.5% of theta for 262,144 elements, which leaves
-// 0.3% of normally distributed elements open.  A threshold outside its window
-// costs a second read of that worker's rows, not a result.
-__global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_stats* win, int most) {
+// The mean |g| of a sample of a worker's eligible elements in a bucket, at
+// most `most` words, one from each of as many stretches of the bucket (so that
+// every parameter's scale is met), at a place of its own in each.  The
+// threshold is tau times the whole bucket's mean; with S1 and S2 the sample's
+// sums of |g| and g*g, a mean over independent elements is off by less than
+// sqrt(S2) / S1 of itself (one deviation; for normal values 1.25 / sqrt(m),
+// and truly 0.75 / sqrt(m)), and the window is two of these wide on either
+// side: about 0.5% of theta for 262,144 elements, which leaves 0.3% of normally
+// distributed elements open.  A threshold outside its window costs a second
+// read of that worker's rows, not a result.
+//
+// Block (worker, bucket, part): every np-th kSampleBlock of the sampled words,
+// to a slot of pass 1's partials that pass 1 has yet to write (sabs S1, ssq S2,
+// sabs_c the elements, nonfinite whether there is any).  A block is a chain of
+// scattered reads: with one per worker and bucket, 8 workers of 1.5 GB took
+// 106 us, 64 of 8 GB 86.
+__global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_tsample(TernArgs a, Partial* sample, int most) {
   __shared__ double r1[kWaves], r2[kWaves];
   __shared__ uint32_t rn[kWaves], rbad[kWaves];
   const int w = blockIdx.x, b = blockIdx.y;
   const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   int64_t base, nbe, chunk0;
-  bucket_span(b, a.btab, a.n_total, a.bucket_n, 0, base, nbe, chunk0);
+  bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
+  const int np = sample_parts(nbe, most, a.chunk);
+  if ((int)blockIdx.z >= np) return;  // whole block
   const float* row = a.g + (int64_t)w * a.wstride + base;
   const int64_t nw = (nbe + 63) / 64;
-  int64_t ns = nw <= 64 ? nw : nw / 24;  // sampled words: 4%, 64 to `most`
-  if (nw > 64 && ns < 64) ns = 64;
-  if (ns > most) {
-    // few blocks: a large bucket's window is worth a longer sample
-    const int64_t more = most < kSampleWords ? nw / 64 : 0;
-    ns = more > most ? (more < 4 * kSampleWords ? more : 4 * kSampleWords) : most;
-  }
+  const int64_t ns = sample_words(nw, most);
   double s1 = 0.0, s2 = 0.0;
   uint32_t n = 0;
   bool bad = false;
-  constexpr int NL = 32;  // words in flight
+  constexpr int NL = kSampleBlock / kWaves;  // words of a wavefront, all in flight
 #pragma unroll 1
-  for (int64_t j0 = v * 64; j0 < ns; j0 += kThreads1) {
+  for (int64_t j0 = (int64_t)blockIdx.z * kSampleBlock + v * NL; j0 < ns; j0 += np * kSampleBlock) {
     // this lane's sampled word, from stretch j of ns, and its mask word
-    const int64_t j = j0 + lane;
-    int64_t k = 0;
-    uint64_t m = 0;
-    if (j < ns) {
-      k = (j * nw + (int64_t)((uint32_t)j * 2654435761u >> 8) % nw) / ns;
-      m = a.mask[base / 64 + k] & low_bits(nbe - 64 * k);
+    const int64_t j = j0 + (lane & (NL - 1));
+    const bool some = lane < NL && j < ns;
+    const int64_t k = j < ns ? (j * nw + (int64_t)((uint32_t)j * 2654435761u >> 8) % nw) / ns : 0;
+    const uint64_t m = some ? a.mask[base / 64 + k] & low_bits(nbe - 64 * k) : 0;
+    float x[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int64_t e = 64 * (int64_t)__builtin_amdgcn_readlane((int)k, u) + lane;
+      x[u] = row[e < nbe ? e : nbe - 1];
     }
     n += (uint32_t)__popcll(m);
-    const int mine = ns - j0 < 64 ? (int)(ns - j0) : 64;  // words of this wavefront
-#pragma unroll 1
-    for (int i = 0; i < mine; i += NL) {
-      float x[NL];
-      float f1 = 0.0f, f2 = 0.0f;  // FP32 will do for the window (all in FP64 took half the kernel's time)
+    float f1 = 0.0f, f2 = 0.0f;  // FP32 will do for the window (all in FP64 took half the kernel's time)
 #pragma unroll
-      for (int u = 0; u < NL; ++u) {
-        const int64_t e = 64 * (int64_t)__builtin_amdgcn_readlane((int)k, i + u) + lane;
-        x[u] = row[e < nbe ? e : nbe - 1];
-      }
-#pragma unroll
-      for (int u = 0; u < NL; ++u) {
-        const uint64_t mu = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(m >> 32), i + u) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((uint32_t)m, i + u);
-        const bool fin = finite32(x[u]);
-        bad |= !fin;
-        const float d = __builtin_amdgcn_inverse_ballot_w64(mu) && fin ? x[u] : 0.0f;
-        f1 += __builtin_fabsf(d);
-        f2 = __builtin_fmaf(d, d, f2);
-      }
-      s1 += (double)f1;
-      s2 += (double)f2;
+    for (int u = 0; u < NL; ++u) {
+      const uint64_t mu = ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(m >> 32), u) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((uint32_t)m, u);
+      const bool fin = finite32(x[u]);
+      bad |= !fin;
+      const float d = __builtin_amdgcn_inverse_ballot_w64(mu) && fin ? x[u] : 0.0f;
+      f1 += __builtin_fabsf(d);
+      f2 = __builtin_fmaf(d, d, f2);
     }
+    s1 += (double)f1;
+    s2 += (double)f2;
   }
   s1 = wave_sum(s1);
   s2 = wave_sum(s2);
@@ -101,19 +97,78 @@ __global__ __launch_bounds__(kThreads1) void k_twindow(TernArgs a, nf_worker_sta
       t2 += r2[i];
       tn += (double)rn[i];
     }
+    Partial p;
+    p.sabs = t1;
+    p.ssq = t2;
+    p.nonfinite = some_bad;
+    p.sabs_c = tn;
+    p.sabs_b = 0.0;
+    sample[(chunk0 + blockIdx.z) * a.W + w] = p;
+  }
+}
+
+// The windows of a bucket, a thread a worker, and whether the sample foretells
+// the fallback (see Window).  A launch of its own, so that pass 1 knows from
+// its first chunk on.
+__global__ __launch_bounds__(256) void k_twindow(TernArgs a, const Partial* sample, nf_worker_stats* win, int most,
+                                                 float ratio) {
+  __shared__ float power[256];
+  const int b = blockIdx.x, w = threadIdx.x;
+  int64_t base, nbe, chunk0;
+  bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
+  const int64_t nw = (nbe + 63) / 64;
+  const int np = sample_parts(nbe, most, a.chunk);
+  float* f = reinterpret_cast<float*>(win + (int64_t)b * a.W + w);
+  if (w < a.W) {
+    double t1 = 0.0, t2 = 0.0, tn = 0.0;
+    uint64_t some_bad = 0;
+#pragma unroll 8
+    for (int p = 0; p < np; ++p) {
+      const Partial q = sample[(chunk0 + p) * a.W + w];
+      t1 += q.sabs;
+      t2 += q.ssq;
+      tn += q.sabs_c;
+      some_bad |= q.nonfinite;
+    }
     // a point where the sample says too little: the worker is read again
     double theta = 0.0, eps = 0.0;
     if (t1 > 0.0) {
       theta = (double)a.tau * (t1 / tn);
-      eps = ns == nw ? 1e-5 : 2.0 * sqrt(t2) / t1;
+      eps = sample_words(nw, most) == nw ? 1e-5 : 2.0 * sqrt(t2) / t1;
       if (!(eps < 0.25)) eps = 0.0;
     }
-    float* f = reinterpret_cast<float*>(win + (int64_t)b * a.W + w);
+    power[w] = t1 > 0.0 && !some_bad ? (float)(t2 / tn) : -1.0f;
     f[0] = (float)(theta * (1.0 - eps));
     f[1] = (float)(theta * (1.0 + eps));
-    f[2] = t1 > 0.0 && !some_bad ? (float)(t2 / tn) : -1.0f;
+    f[2] = power[w];
     f[3] = 0.0f;
   }
+  __syncthreads();
+  if (w >= 64 || ratio < 0.0f) return;
+  // one wavefront
+  uint32_t most_power = 0;  // as bits: from 0 on they are ordered alike
+  bool bad = false;
+#pragma unroll 1
+  for (int i = w; i < a.W; i += 64) {
+    const uint32_t u = __float_as_uint(power[i]);
+    bad |= power[i] < 0.0f;
+    most_power = power[i] >= 0.0f && u > most_power ? u : most_power;
+  }
+  group_steps(64, [&](auto step) {
+    const uint32_t y = step.of(most_power);
+    most_power = y > most_power ? y : most_power;
+  });
+  const float top = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)most_power, 63));
+  // the largest above `ratio` times the lower median: more than half of the
+  // workers are that far below it
+  int below = 0;
+#pragma unroll 1
+  for (int i0 = 0; i0 < a.W; i0 += 64) {
+    const int i = i0 + w;
+    below += __popcll(__ballot(i < a.W && ratio * power[i < a.W ? i : 0] < top));
+  }
+  const bool ahead = __ballot(bad) != 0 || below > (a.W - 1) / 2;
+  if (ahead && w == 0) f[3] = 1.0f;
 }
 
 // ---------------------------------------------------------------- G-Ternary
@@ -620,9 +675,16 @@ hipError_t launch_ternary_pack(const Geometry& geo, const TernArgs& a0, hipStrea
   return hipSuccess;
 }
 
-hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a, nf_worker_stats* win, hipStream_t s) {
-  hipLaunchKernelGGL(k_twindow, dim3((unsigned)geo.W, (unsigned)geo.nb), dim3(kThreads1), 0, s, a, win,
-                     geo.nb * geo.W >= 128 ? kSampleWords : kSampleWords / 4);
+hipError_t launch_ternary_window(const Geometry& geo, const TernArgs& a0, Partial* sample, nf_worker_stats* win,
+                                 float ratio, hipStream_t s) {
+  TernArgs a = a0;
+  a.chunk = geo.tile * geo.G;
+  const int most = geo.nb * geo.W >= 128 ? kSampleWords : kSampleWords / 4;
+  const dim3 grid((unsigned)geo.W, (unsigned)geo.nb, (unsigned)sample_parts(geo.max_len, most, a.chunk));
+  hipLaunchKernelGGL(k_tsample, grid, dim3(kThreads1), 0, s, a, sample, most);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_twindow, dim3((unsigned)geo.nb), dim3(256), 0, s, a, sample, win, most, ratio);
   return hipGetLastError();
 }
 

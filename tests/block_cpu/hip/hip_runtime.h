@@ -26,6 +26,10 @@
 typedef int hipError_t;
 typedef void* hipStream_t;
 
+struct float2 {
+  float x, y;
+};
+
 namespace cpu {
 
 struct Idx {
@@ -201,6 +205,7 @@ inline int vote(int p, int line, bool count) {
 #define __builtin_amdgcn_wave_barrier() ((void)cpu::meet(0, __LINE__))
 #define __builtin_nontemporal_load(p) (*(p))
 #define __HIP_MEMORY_SCOPE_AGENT 0
+#define __HIP_MEMORY_SCOPE_WORKGROUP 0
 #define __hip_atomic_load(p, order, scope) cpu::on_load(p, cpu::blk->cur / 64)
 #define __hip_atomic_store(p, v, order, scope) ((void)(*(p) = (v)))
 #define __popcll(x) __builtin_popcountll(x)

@@ -13,6 +13,7 @@ from tests.test_gpu_ternary import check_ternary_bucket, ternary_route
 
 pytestmark = pytest.mark.gpu
 
+GIB = 1 << 30  # by tiles above, with more than 16 workers
 BYTES = 640 << 20  # planes in one read above, and from eight workers
 # sizes just above it: eight workers by tiles, 24 by rows
 SIZES = [(8, BYTES // 32 + 77), (24, BYTES // 96 + 77)]
@@ -75,3 +76,31 @@ def test_windows_many_workers(W, n, bucket_n):
     res = ternary_route(g, mask, n, pol, bucket_n)
     for b in range(-(-n // bucket_n)):
         check_ternary_bucket(res, g, mask, n, pol, b, bucket_n, f"W={W} bucket {b}")
+
+
+@pytest.mark.parametrize("W,n", [(8, BYTES // 32 + 77), (16, BYTES // 64 + 77), (24, BYTES // 96 + 77),
+                                 (20, GIB // 80 + 4099), (70, GIB // 280 + 4099)])
+@pytest.mark.parametrize("kind", ["spike", "dead", "sampled_inf", "false_spike"])
+def test_foretold_fallback(kind, W, n):
+    """A fallback that the sample foretells packs no planes: bits stay as they were; one that does not come packs
+    them all after all.  By tiles with one (two element groups, one), two and four workers a wavefront, and by rows."""
+    g, mask = data(W, n, n)
+    mask[5000:9000] = 0  # chunks without an eligible element
+    pol = nf.policy(format=nf.NF_FORMAT_TERNARY)
+    el = np.unpackbits(mask.view(np.uint8), bitorder="little")[:n].astype(bool)
+    if kind == "spike":
+        g[W // 2] *= 10
+    elif kind == "dead":
+        g[W - 1] = 0
+    elif kind == "sampled_inf":
+        g[W // 3, :n:97] = -np.inf
+    else:
+        g[W // 2, :n][el] *= 10
+        g[:, :n][:, ~el] *= 1e4
+    res = ternary_route(g, mask, n, pol)
+    route = check_ternary_bucket(res, g, mask, n, pol, 0, n, f"{kind} W={W}")
+    if kind == "false_spike":
+        assert route == nfo.ROUTE_L
+    else:
+        assert route == nfo.ROUTE_F
+        assert (res["bits"] == ~np.uint64(0)).all()
