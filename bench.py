@@ -111,7 +111,7 @@ class HipEvents:
 def kernel_source_sha():
     """Hash of the pass-1 kernel source, its device helpers and the geometry that shapes its launches."""
     h = hashlib.sha256()
-    for name in ("nf_pass1.hip", "nf_device.h", "nf_internal.h"):
+    for name in ("nf_pass1.hip", "nf_device.h", "nf_internal.h", "nf_decide.h"):
         h.update(open(os.path.join(ROOT, "paper_2606_25759_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 
@@ -579,9 +579,11 @@ class Workload:
         nbs = np.diff(self.off)
         ne = d["n_eligible"].astype(np.int64)
         nwb = (nbs + 63) // 64
-        # pass 1: gradients once, mask once, sign words out (G-Binary; both planes where G-Ternary takes one read:
-        # 8 workers and 640 MiB on), FP32 sums at routed positions out
-        one_read = ternary and W >= 8 and 4 * W * n > 640 << 20
+        # pass 1: gradients once, mask once, sign words out (G-Binary; both planes where G-Ternary takes one read),
+        # FP32 sums at routed positions out
+        path = nf.nf_pass1_path(W, n, self.bn, pol.format) if self.bn else \
+            nf.nf_pass1_path_table(W, self.off, pol.format)
+        one_read = bool(path & nf.NF_PASS1_PLANES)
         words = 16 * W if one_read else 0 if ternary else 8 * W
         pass1_bytes = float((4 * W * nbs + 8 * nwb + words * nwb + 4 * (nbs - ne)).sum())
         is_l, is_f = d["route"] == 0, d["route"] == 1
@@ -594,10 +596,9 @@ class Workload:
         else:
             l_bytes = 8 * W * nwb + 8 * nwb + cbytes + 4 * ne
         pass2_bytes = float((l_bytes * is_l).sum() + ((4 * W * ne + 8 * nwb + 4 * ne) * is_f).sum())
-        launches = (nf.nf_pass1_launches(W, n, self.bn, sign_words=not ternary) if self.bn else
-                    nf.nf_pass1_launches_table(W, self.off, sign_words=not ternary))
-        if one_read:  # one launch, or one for each row group
-            launches = 1 if W <= 32 else 2 if W <= 64 else -(-W // 64)
+        kinds = 2 if one_read else not ternary
+        launches = (nf.nf_pass1_launches(W, n, self.bn, sign_words=kinds) if self.bn else
+                    nf.nf_pass1_launches_table(W, self.off, sign_words=kinds))
         # a cold run's wall clock includes the overwrites: its value comes from the device events
         value = self.lay.input_bytes() / ((device_ms if cold else ms_per_step) * 1e-3) / 1e9
         plain_value = None if plain_ms is None else self.lay.input_bytes() / (plain_ms * 1e-3) / 1e9
@@ -619,7 +620,7 @@ class Workload:
             "phases_ms": {"pass1": round(pass1_ms, 4), "decide": round(decide_ms, 4),
                           "pass2": round(pass2_ms, 4), "device_total": round(device_ms, 4),
                           "pass2_algorithmic_gbs": round(pass2_bytes / max(pass2_ms, 1e-9) / 1e6, 1)},
-            "pass1": {"kernel": "k_pass1", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+            "pass1": {"kernel": "k_rows" if path & nf.NF_PASS1_ROWS else "k_pass1", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                       "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "launches_per_step": launches,
                       "algorithmic_bytes_per_launch": round(pass1_bytes / launches),
                       "avg_launch_ms": round(pass1_ms / launches, 5)},
@@ -878,7 +879,7 @@ def config_record(wl, m, pol, cold, cpu, counters):
                                   "device_ms", "phases_ms", "routes", "mgtr")})
     row["unit"] = "GB/s"
     roof = dict(m["pass1"])
-    roof["traffic"] = pass1_traffic(counters)
+    roof["traffic"] = pass1_traffic(counters, roof["kernel"])
     roof["traffic_gbs"] = (None if roof["traffic"] is None else
                            round(roof["traffic"] / (roof["avg_launch_ms"] * 1e-3) / 1e9, 1))
     row["roofline_pass1"] = roof
@@ -900,12 +901,13 @@ def committed_counters(workload, fmt):
     return rec.get("kernels")
 
 
-def pass1_traffic(counters):
-    """HBM bytes per pass-1 launch in a workload's committed counters (the
-    pass-1 instantiation the step ran), or None."""
+def pass1_traffic(counters, kernel):
+    """HBM bytes per launch of the step's pass-1 kernel (k_pass1 or k_rows) in
+    a workload's committed counters (the instantiation the step ran), or
+    None."""
     if not counters:
         return None
-    names = [k for k in counters if k.startswith("k_pass1<")]
+    names = [k for k in counters if k.startswith(kernel + "<")]
     if not names:
         return None
     return counters[max(names, key=lambda k: counters[k]["dispatches"])]["hbm_bytes_per_dispatch"]

@@ -491,9 +491,11 @@ size_t nf_bucket_table_bytes(int32_t W, const int64_t* bucket_offsets, int32_t n
 nf_status nf_bucket_table_init(int32_t W, const int64_t* bucket_offsets, int32_t nb, void* table,
                                size_t table_bytes, void* stream);
 size_t nf_workspace_bytes_table(int32_t W, const int64_t* bucket_offsets, int32_t nb);
-/* Profiling query (no paper counterpart): nf_pass1_launches for a bucket
- * table; 0 for invalid offsets or W.  Pure host function. */
+/* Profiling queries (no paper counterpart): nf_pass1_launches and
+ * nf_pass1_path for a bucket table; 0 for invalid offsets or W.  Pure host
+ * functions. */
 int64_t nf_pass1_launches_table(int32_t W, const int64_t* bucket_offsets, int32_t nb, int32_t sign_words);
+int32_t nf_pass1_path_table(int32_t W, const int64_t* bucket_offsets, int32_t nb, int32_t format);
 nf_status nf_route_bucket_table(const float* grads, int64_t worker_stride, int32_t W,
                                 const int64_t* bucket_offsets, int32_t nb, const void* table,
                                 const uint64_t* mask, const nf_route_policy* policy_host, uint64_t* bits,
@@ -607,8 +609,8 @@ nf_status nf_endpoint_guard(const nf_endpoint_model* model_host, int64_t n, int6
  * passed as void*) on their stream: before pass 1, after pass 1, after the
  * decision kernel and after pass 2 (the last one also when pass 2 is not
  * needed; a small problem decides and runs its read side in one launch, after
- * which both are recorded).  The caller owns the events; passing four NULLs turns recording
- * off.  Events are recorded, never synchronised, so calls stay asynchronous.
+ * which both are recorded).  The caller owns the events; passing four NULLs
+ * turns recording off.  Events are recorded, never synchronised, so calls stay asynchronous.
  */
 nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after_decide,
                               void* after_pass2);
@@ -619,13 +621,26 @@ nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after
  * runs as one launch for a problem of at most 4,096 element chunks, else in
  * launches of a fixed number of chunks, and above 32 workers, but for the
  * smallest problems, once per row group or in as many shares of the
- * chunks).  sign_words = 1
- * for a pass 1 that packs sign words (G-Binary), 0 for one that does not
- * (G-Ternary's first of two reads, nf_bucket_health), which runs in bigger
- * launches; one that packs the G-Ternary planes runs as one launch per row
- * group.  0 for n_total = 0 or invalid sizes.  Pure host function.
+ * chunks).  sign_words = 1 for a pass 1 that packs sign words (G-Binary), 0
+ * for one that does not (G-Ternary's first of two reads, nf_bucket_health),
+ * which runs in bigger launches, 2 for one that packs the G-Ternary planes
+ * (NF_PASS1_PLANES), one launch per row group.  0 for n_total = 0 or invalid
+ * sizes.  Pure host function.
  */
 int64_t nf_pass1_launches(int32_t W, int64_t n_total, int64_t bucket_n, int32_t sign_words);
+
+/*
+ * Profiling query (no paper counterpart): which kernels a route call of these
+ * sizes runs when its policy does not fix the route, as a sum of NF_PASS1_*;
+ * format: NF_FORMAT_BINARY or NF_FORMAT_TERNARY.  0 also for n_total = 0 or
+ * invalid sizes.  Pure host function.
+ */
+enum {
+  NF_PASS1_ROWS = 1,   /* pass 1 by rows (k_rows), else by tiles (k_pass1)      */
+  NF_PASS1_PLANES = 2, /* it packs both G-Ternary planes: one read, not two     */
+  NF_PASS1_FUSED = 4   /* decision and read side in one launch (k_small2)       */
+};
+int32_t nf_pass1_path(int32_t W, int64_t n_total, int64_t bucket_n, int32_t format);
 
 /*
  * Geometry query (no paper counterpart): the number of elements of every

@@ -27,14 +27,15 @@ NF_DECODE_SOFT, NF_DECODE_MAJORITY = 0, 1
 NF_FP32_SUM, NF_FP32_MEAN = 0, 1
 NF_SEL_ROUTED, NF_SEL_ELIGIBLE, NF_SEL_ALL = 0, 1, 2
 NF_FORMAT_BINARY, NF_FORMAT_TERNARY = 0, 1
+NF_PASS1_ROWS, NF_PASS1_PLANES, NF_PASS1_FUSED = 1, 2, 4
 
 # Exported names, in the order include/nf.h declares them.
 EXPORTS = ["nf_abi_version", "nf_last_error", "nf_mask_from_segments", "nf_workspace_bytes",
            "nf_bucket_health", "nf_pack_signs", "nf_fp32_reduce", "nf_signcount_reduce",
            "nf_route_decide", "nf_route_bucket", "nf_workspace_bytes_buckets", "nf_route_buckets",
            "nf_route_buckets_noalloc", "nf_bucket_table_bytes", "nf_bucket_table_init",
-           "nf_workspace_bytes_table", "nf_pass1_launches_table", "nf_route_bucket_table",
-           "nf_set_phase_events", "nf_pass1_launches", "nf_pass1_chunk_elems", "nf_slice_scales_from_pass1", "nf_ternary_threshold", "nf_pack_ternary",
+           "nf_workspace_bytes_table", "nf_pass1_launches_table", "nf_pass1_path_table", "nf_route_bucket_table",
+           "nf_set_phase_events", "nf_pass1_launches", "nf_pass1_path", "nf_pass1_chunk_elems", "nf_slice_scales_from_pass1", "nf_ternary_threshold", "nf_pack_ternary",
            "nf_ternary_reduce", "nf_partial_counts", "nf_partial_count_reduce", "nf_stock_signcount",
            "nf_supervisor_init", "nf_supervisor_policy", "nf_supervisor_update", "nf_endpoint_guard",
            "nf_sliced_layout_sizes", "nf_sliced_layout", "nf_compact_signs", "nf_slice_workspace_bytes",
@@ -139,11 +140,13 @@ def load(path=None):
         "nf_bucket_table_init": (ctypes.c_int, [_I32, _P, _I32, _P, _SZ, _P]),
         "nf_workspace_bytes_table": (_SZ, [_I32, _P, _I32]),
         "nf_pass1_launches_table": (_I64, [_I32, _P, _I32, _I32]),
+        "nf_pass1_path_table": (_I32, [_I32, _P, _I32, _I32]),
         "nf_route_bucket_table": (ctypes.c_int, [_P, _I64, _I32, _P, _I32, _P, _P, _P, _P, _I64, _P, _P,
                                                  _P, _P, _P, _SZ, _P]),
         "nf_set_phase_events": (ctypes.c_int, [_P, _P, _P, _P]),
         "nf_slice_scales_from_pass1": (_I32, [_P, _I64, _I32, _I64, _P, _P, _I64, _P, _P, _P, _SZ, _P]),
         "nf_pass1_launches": (_I64, [_I32, _I64, _I64, _I32]),
+        "nf_pass1_path": (_I32, [_I32, _I64, _I64, _I32]),
         "nf_pass1_chunk_elems": (_I64, [_I32, _I64, _I64, _P]),
         "nf_ternary_threshold": (ctypes.c_int, [_P, _I32, _I64, ctypes.c_float, _P]),
         "nf_pack_ternary": (ctypes.c_int, [_P, _I64, _I32, _I64, _P, _P, _P, _I64, _P]),
@@ -537,7 +540,12 @@ def nf_workspace_bytes_table(W, offsets):
 
 def nf_pass1_launches_table(W, offsets, sign_words=True):
     o, p, nb = _offsets(offsets)
-    return int(load().nf_pass1_launches_table(W, p, nb, int(bool(sign_words))))
+    return int(load().nf_pass1_launches_table(W, p, nb, int(sign_words)))
+
+
+def nf_pass1_path_table(W, offsets, format=NF_FORMAT_BINARY):
+    o, p, nb = _offsets(offsets)
+    return int(load().nf_pass1_path_table(W, p, nb, format))
 
 
 def nf_route_bucket_table(grads, offsets, table, mask, pol, bits, counts, out, stats, decisions, ws,
@@ -561,8 +569,14 @@ def nf_set_phase_events(before_pass1=None, after_pass1=None, after_decide=None, 
 
 def nf_pass1_launches(W, n_total, bucket_n, sign_words=True):
     """Pass-1 kernel launches of one nf_route_buckets call (profiling); pass
-    sign_words=False for a pass 1 without sign words (G-Ternary, health)."""
-    return int(load().nf_pass1_launches(W, n_total, bucket_n, int(bool(sign_words))))
+    sign_words=False for a pass 1 without sign words (G-Ternary's first of two
+    reads, health), 2 for one that packs the G-Ternary planes."""
+    return int(load().nf_pass1_launches(W, n_total, bucket_n, int(sign_words)))
+
+
+def nf_pass1_path(W, n_total, bucket_n, format=NF_FORMAT_BINARY):
+    """NF_PASS1_* of a route call with these sizes (profiling)."""
+    return int(load().nf_pass1_path(W, n_total, bucket_n, format))
 
 
 def nf_pass1_chunk_elems(W, n_total, bucket_n):

@@ -306,7 +306,7 @@ nf_status route_geo(const nf::Geometry& geo, const float* g, int64_t stride, int
   t.bpb2 = geo.bpb2;
   t.btab = btab;
   t.cbucket = cbucket;
-  const bool planes = ternary && !predecided && !fuse && nf::planes_in_one_read(geo);
+  const bool planes = ternary && !predecided && (nf::pass1_path(geo, true) & NF_PASS1_PLANES);
   NF_TRY(run_pass1_decide(geo, g, stride, mask, (predecided || ternary) ? nullptr : bits, bstride, out,
                           predecided ? nf::kSumsAll : nf::kSumsRouted, pol->fp32_op == NF_FP32_MEAN,
                           stats, dec, pol, ws, s, true, btab, cbucket, fuse ? &f : nullptr, planes ? &t : nullptr));
@@ -390,8 +390,12 @@ nf_status nf_set_phase_events(void* before_pass1, void* after_pass1, void* after
 
 int64_t nf_pass1_launches(int32_t W, int64_t n_total, int64_t bucket_n, int32_t sign_words) {
   if (W < 1 || W > 255 || n_total <= 0 || bucket_n <= 0) return 0;
-  const nf::Geometry geo = nf::make_geometry(W, n_total, bucket_n);
-  return nf::pass1_launches(geo, sign_words != 0);
+  return nf::pass1_launches(nf::make_geometry(W, n_total, bucket_n), sign_words);
+}
+
+int32_t nf_pass1_path(int32_t W, int64_t n_total, int64_t bucket_n, int32_t format) {
+  if (W < 1 || W > 255 || n_total <= 0 || bucket_n <= 0) return 0;
+  return nf::pass1_path(nf::make_geometry(W, n_total, bucket_n), format == NF_FORMAT_TERNARY);
 }
 
 int64_t nf_pass1_chunk_elems(int32_t W, int64_t n_total, int64_t bucket_n, int64_t* chunks_per_bucket) {
@@ -1013,8 +1017,12 @@ nf_status nf_bucket_table_init(int32_t W, const int64_t* bucket_offsets, int32_t
 
 int64_t nf_pass1_launches_table(int32_t W, const int64_t* bucket_offsets, int32_t nb, int32_t sign_words) {
   if (W < 1 || W > 255 || check_table_offsets(bucket_offsets, nb) != NF_OK) return 0;
-  const nf::Geometry geo = nf::make_geometry_table(W, bucket_offsets, nb);
-  return nf::pass1_launches(geo, sign_words != 0);
+  return nf::pass1_launches(nf::make_geometry_table(W, bucket_offsets, nb), sign_words);
+}
+
+int32_t nf_pass1_path_table(int32_t W, const int64_t* bucket_offsets, int32_t nb, int32_t format) {
+  if (W < 1 || W > 255 || check_table_offsets(bucket_offsets, nb) != NF_OK) return 0;
+  return nf::pass1_path(nf::make_geometry_table(W, bucket_offsets, nb), format == NF_FORMAT_TERNARY);
 }
 
 size_t nf_workspace_bytes_table(int32_t W, const int64_t* bucket_offsets, int32_t nb) {

@@ -99,12 +99,11 @@ inline int64_t one_launch_epoch(int64_t total_chunks) {
   return total_chunks <= kOneLaunchChunks ? (total_chunks > 0 ? total_chunks : 1) : kEpochBlocks;
 }
 
-// Small problems take kernels of their own (nf_small.hip): those that get one
-// chunk per compute unit by the rule above.
 // Partials (slots times workers) of a bucket that every read-side block of a
 // small problem reduces for itself; with more, the decision is a launch of
 // its own.  4,096 are 160 KB, read from the caches by each block.
 constexpr int64_t kSmallPartials = 4096;
+constexpr int kSmallWorkers = 64;  // ... and its workers: a lane each
 
 // Pass 2: a wavefront takes 64 consecutive bitmap words (4096 elements) per
 // step, four wavefronts per block.
@@ -157,6 +156,9 @@ inline int64_t pass1_launch_chunks(const Geometry& g, bool sign_words) {
   return sign_words || g.total_chunks <= kOneLaunchChunks ? pass1_epoch(g) : kEpochNoPack;
 }
 
+// Small problems, those that get one chunk per compute unit (kSmallFillChunks),
+// take a pass 1 (k_rows) and, where small_decide says so, a read side (k_small2)
+// of their own.
 inline bool small_problem(const Geometry& g) {
   return g.total_chunks > 0 && g.total_tiles <= kFillChunks &&
          (int64_t)g.W * g.G * g.tile / 64 <= kBitsWords + kBitsWords / 2;  // all rows' sign words in LDS
@@ -177,7 +179,17 @@ inline int64_t gradient_bytes(const Geometry& g) { return 4 * (int64_t)g.W * g.n
 // element better (W = 32: 2.8 GB of runs 639 us, by rows 690; W = 16, a
 // Transformer's 5.5 GB 1.16 ms, by rows 1.28).  Above 16 workers its mixed
 // chunks go one tile at a time, and in launches of 256 chunks (above
-// kOneLaunchChunks) the slowest of them holds up each launch.
+// kOneLaunchChunks) the slowest of them holds up each launch: there by rows
+// takes 45 to 64% of the time on conv (17 workers 6 GB 2.85 -> 1.28 ms, 32
+// workers 11.5 GB 3.76 -> 2.39) and, on runs, from 86% (48 workers, 7 GB 1.86 ->
+// 1.59) to 105% (32 workers, 11.5 GB 2.51 -> 2.64 ms).
+// FP32 sums at every position (a vetoed step) read every gradient twice by
+// rows, and still take 60 to 90% of the time through the stage: W = 16, 80 MB
+// 77 -> 54 us; 17, 1 GB 666 -> 402; 24, 9 GB 4.43 -> 3.67 ms; 48, 6 GB 3.03 ->
+// 2.73; 255, 0.9 GB 726 -> 455 us.  So the sum mode does not enter the rule.
+// Above kRowsChunks nothing was measured by rows but a loss of a few percent on
+// runs at its edge; conv pays for the line: 17 workers 9 GB, 4.18 ms by tiles,
+// against 1.28 for 6 GB by rows.
 constexpr int64_t kRowsBytes = 160ll << 20;
 constexpr int64_t kRowsBytesWide = 1ll << 30;  // above 16 workers
 constexpr int64_t kRowsChunks = 12000;         // 17 to 64 workers, above kOneLaunchChunks
@@ -187,7 +199,7 @@ inline bool rows_problem(const Geometry& g) {
   return g.W > kWaves && g.W <= kRowGroup && g.total_chunks > kOneLaunchChunks && g.total_chunks <= kRowsChunks;
 }
 inline bool small_decide(const Geometry& g) {
-  return small_problem(g) && g.W <= 64 && g.chunks_full * g.W <= kSmallPartials && g.gs == 0;
+  return small_problem(g) && g.W <= kSmallWorkers && g.chunks_full * g.W <= kSmallPartials && g.gs == 0;
 }
 // Pass 1 by rows: items per worker (every parts-th eight of its words each)
 // for a chunk of `eights` times eight words.  The wavefronts take the items
@@ -216,13 +228,21 @@ inline int pass1_parts(int rows, int eights) {
 // ms; with few workers the count weighs more (W = 2, 1 GB 643 -> 721 us).
 constexpr int64_t kOneReadBytes = 640ll << 20;
 constexpr int kOneReadWorkers = 8;
+static_assert(kOneReadBytes >= kCachedBytes, "planes in one read: by rows only without cached loads");
 inline bool planes_in_one_read(const Geometry& g) {
   return g.total_chunks > 0 && g.W >= kOneReadWorkers && gradient_bytes(g) > kOneReadBytes;
 }
-// Launches of pass 1.
-inline int64_t pass1_launches(const Geometry& g, bool sign_words) {
+// Launches of pass 1; words: 0 none, 1 sign words, 2 both G-Ternary planes.
+inline int64_t pass1_launches(const Geometry& g, int words) {
   if (rows_problem(g)) return small_problem(g) ? 1 : g.ngroups;
-  return g.ngroups * ceil_div(g.total_chunks, pass1_launch_chunks(g, sign_words));
+  if (words == 2) return g.ngroups;
+  return g.ngroups * ceil_div(g.total_chunks, pass1_launch_chunks(g, words != 0));
+}
+// NF_PASS1_* of a route that the policy does not fix.
+inline int32_t pass1_path(const Geometry& g, bool ternary) {
+  const bool fused = small_decide(g);
+  return (rows_problem(g) ? NF_PASS1_ROWS : 0) | (ternary && !fused && planes_in_one_read(g) ? NF_PASS1_PLANES : 0) |
+         (fused ? NF_PASS1_FUSED : 0);
 }
 
 // Row group i of a geometry: its first worker and its rows (the first

@@ -1,5 +1,5 @@
-// nf_rows.h - a chunk of pass 1 by rows (k_pass1's mixed and ragged chunks,
-// every chunk of a small problem).
+// nf_rows.h - a chunk of pass 1 by rows (k_rows, which takes every chunk of the
+// problems that rows_problem names).
 #pragma once
 
 #include "nf_decide.h"

@@ -1,5 +1,8 @@
-// nf_rows.hip - pass 1 by rows (gfx950): small problems, and those whose
-// chunks k_pass1 would take by its slower loops (rows_problem).
+// nf_rows.hip - pass 1 by rows (k_rows, gfx950): small problems, and those
+// whose chunks k_pass1 would take by its slower loops (rows_problem).  8 KiB
+// of code a variant: k_pass1's four unrolled loops are 34, of which a block of
+// one or two tiles runs every line once (on a bucket of 8 x 70,001 elements,
+// 11 of its 17 us between the first loads and the last store, on one tile).
 #include <hip/hip_ext.h>
 
 #include "nf_rows.h"
@@ -29,7 +32,7 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a0, hipStream_t s) 
   const bool cached = small || gradient_bytes(geo) <= kCachedBytes;
   const bool tern = a0.nbits != nullptr, pack = a0.bits && !tern;
   const auto kernel =
-      tern ? (cached ? k_rows<false, true, false, true> : k_rows<false, true, false, false>)
+      tern ? k_rows<false, true, false, false>  // above kOneReadBytes
       : pack ? (small ? k_rows<true, false, true, true> : cached ? k_rows<true, false, false, true> : k_rows<true, false, false, false>)
              : (small ? k_rows<false, false, true, true> : cached ? k_rows<false, false, false, true> : k_rows<false, false, false, false>);
   Pass1Args a = a0;
@@ -40,7 +43,7 @@ hipError_t launch_rows(const Geometry& geo, const Pass1Args& a0, hipStream_t s) 
   // row group of every chunk, in order where the FP32 sums go from one
   // group to the next.
   const bool by_group = !small && geo.W > kRowGroup;
-  const int launches = (int)pass1_launches(geo, a.bits != nullptr);
+  const int launches = (int)pass1_launches(geo, tern ? 2 : pack);
   for (int i = 0; i < launches; ++i) {
     int wb = 0, rows = geo.W;
     int64_t q0 = 0, q1 = geo.total_chunks;

@@ -1,20 +1,14 @@
-// nf_small.hip - the reducer's two kernels for small problems (gfx950).
-//
-//   k_rows  write side of a small problem: pass 1's chunks, partials and
-//             outputs, by code that fits a few instruction-cache lines
-//   k_small2  decision and read side in one launch: every block reduces its
-//             bucket's partials and decides the route itself, then counts
-//             and decodes, packs and counts the G-Ternary planes, or adds
-//             the workers in FP32
+// nf_small.hip - decision and read side of a small problem in one launch
+// (k_small2, gfx950): every block reduces its bucket's partials and decides
+// the route itself, then counts and decodes, packs and counts the G-Ternary
+// planes, or adds the workers in FP32.  Its write side is k_rows
+// (nf_rows.hip).
 //
 // A small problem is one whose time is latency, not bandwidth: a few hundred
 // chunks at most, one per compute unit (small_problem, nf_internal.h).
 // Its gradients stay in the caches, so reading an element twice costs
 // little, while every dependent step (a launch, a block barrier, a first
-// fetch of an instruction line) costs a microsecond.  k_pass1's four
-// unrolled loops are 34 KiB of code of which a block of one or two tiles
-// runs every line once: on a bucket of 8 x 70,001 elements it spent 11 of its
-// 17 us between its first loads and its last store, on one tile.
+// fetch of an instruction line) costs a microsecond.
 #include <hip/hip_ext.h>
 
 #include "nf_decide.h"
@@ -39,13 +33,13 @@ namespace nf {
 template <bool TERNARY>
 __global__ __launch_bounds__(kThreads2) void k_small2(Small2Args a) {
   constexpr bool EXACT = TERNARY;
-  __shared__ nf_worker_stats st[256];
+  __shared__ nf_worker_stats st[kSmallWorkers];
   __shared__ unsigned long long hist[256];
   __shared__ nf_route_decision dec;
   __shared__ uint64_t ne_s;
-  __shared__ uint8_t redo[256];
-  __shared__ float tab[2 * 255 + 1];
-  __shared__ float th[256];
+  __shared__ uint8_t redo[kSmallWorkers];
+  __shared__ float tab[2 * kSmallWorkers + 1];
+  __shared__ float th[kSmallWorkers];
   const DecideArgs& d = a.d;
   const int b = blockIdx.y;
   const int W = d.W;
@@ -184,32 +178,29 @@ __global__ __launch_bounds__(kThreads2) void k_small2(Small2Args a) {
       const int64_t e = base + 64 * k + lane;
       const float* p = d.g + (live ? e : base + nbe - 1);
       int cp = 0, cn = 0;
-      for (int w0 = 0; w0 < W; w0 += 64) {
-        // the planes' words of workers w0 + l, gathered in lane l
-        uint64_t pw = 0, nw = 0;
-        const int wn = W - w0 < 64 ? W - w0 : 64;
+      // the planes' words of worker l, gathered in lane l
+      uint64_t pw = 0, nw = 0;
 #pragma unroll 1
-        for (int i0 = 0; i0 < wn; i0 += 8) {
-          float x[8];
+      for (int i0 = 0; i0 < W; i0 += 8) {
+        float x[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(w0 + (i0 + u < wn ? i0 + u : wn - 1)) * d.wstride];
+        for (int u = 0; u < 8; ++u) x[u] = p[(int64_t)(i0 + u < W ? i0 + u : W - 1) * d.wstride];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u;
-            const uint64_t mi = i < wn ? m : 0;
-            const bool keep = !(__builtin_fabsf(x[u]) < th[w0 + (i < wn ? i : 0)]);  // gated to 0 below the threshold
-            const uint64_t pb = __ballot(keep && x[u] > 0.0f) & mi;
-            const uint64_t nb = __ballot(keep && x[u] < 0.0f) & mi;
-            pw = lane == i ? pb : pw;
-            nw = lane == i ? nb : nw;
-            cp = (int)add_lane_bit((uint32_t)cp, pb);
-            cn = (int)add_lane_bit((uint32_t)cn, nb);
-          }
+        for (int u = 0; u < 8; ++u) {
+          const int i = i0 + u;
+          const uint64_t mi = i < W ? m : 0;
+          const bool keep = !(__builtin_fabsf(x[u]) < th[i < W ? i : 0]);  // gated to 0 below the threshold
+          const uint64_t pb = __ballot(keep && x[u] > 0.0f) & mi;
+          const uint64_t nb = __ballot(keep && x[u] < 0.0f) & mi;
+          pw = lane == i ? pb : pw;
+          nw = lane == i ? nb : nw;
+          cp = (int)add_lane_bit((uint32_t)cp, pb);
+          cn = (int)add_lane_bit((uint32_t)cn, nb);
         }
-        if (lane < wn) {
-          pbits[(int64_t)(w0 + lane) * a.bstride + k] = pw;
-          nbits[(int64_t)(w0 + lane) * a.bstride + k] = nw;
-        }
+      }
+      if (lane < W) {
+        pbits[(int64_t)lane * a.bstride + k] = pw;
+        nbits[(int64_t)lane * a.bstride + k] = nw;
       }
       if (live) {
         if (a.counts) {

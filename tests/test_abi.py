@@ -299,6 +299,39 @@ def test_pass1_launch_counts():
     assert nf.nf_pass1_launches(256, 100, 100) == 0
 
 
+def test_pass1_paths():
+    """Which kernels a route takes, at both sides of each line, and its launches."""
+    R, P, F = nf.NF_PASS1_ROWS, nf.NF_PASS1_PLANES, nf.NF_PASS1_FUSED
+    mb, tern = 1 << 20, nf.NF_FORMAT_TERNARY
+
+    def path(W, nbytes, fmt=nf.NF_FORMAT_BINARY):
+        n = nbytes // (4 * W)
+        off = np.array([0, n], np.int64)
+        got = nf.nf_pass1_path(W, n, n, fmt)
+        assert got == nf.nf_pass1_path_table(W, off, fmt)
+        for words in (0, 1, 2):
+            assert nf.nf_pass1_launches(W, n, n, sign_words=words) == nf.nf_pass1_launches_table(W, off, sign_words=words)
+        return got
+
+    # small problems: by rows, with the decision in the read side's launch up to 64 workers and 4,096 partials
+    assert path(8, 2 * mb) == path(64, 4 * mb) == path(1, 4) == R | F
+    assert path(64, 5 * mb) == path(65, mb) == path(255, 16 * mb) == R
+    # 160 MiB up to 16 workers, 1 GiB above
+    assert path(16, 160 * mb) == path(17, 1024 * mb) == path(255, 1024 * mb) == R
+    assert path(16, 161 * mb) == path(17, 1025 * mb) == path(255, 1025 * mb) == 0
+    # 17 to 64 workers: 4,097 to 12,000 chunks by rows
+    for W in (17, 40, 64):
+        chunk, _ = nf.nf_pass1_chunk_elems(W, 1 << 30, 1 << 30)
+        assert [nf.nf_pass1_path(W, k * chunk, k * chunk) for k in (4096, 4097, 12_000, 12_001)] == [0, R, R, 0]
+    # G-Ternary planes in one read: from 8 workers, above 640 MiB
+    assert path(7, 2048 * mb, tern) == path(8, 640 * mb, tern) == 0
+    assert path(8, 641 * mb, tern) == P and path(24, 641 * mb, tern) == R | P and path(8, 641 * mb) == 0
+    assert nf.nf_pass1_launches(8, 1 << 30, 1 << 30, sign_words=2) == 1
+    assert nf.nf_pass1_launches(64, 1 << 28, 1 << 28, sign_words=2) == 2
+    assert nf.nf_pass1_launches(255, 1 << 26, 1 << 26, sign_words=2) == 4
+    assert nf.nf_pass1_path(0, 100, 100) == nf.nf_pass1_path(16, 0, 100) == nf.nf_pass1_path(256, 100, 100) == 0
+
+
 def test_pass1_chunk_geometry():
     # W = 16: tiles of 512 elements, 32 per chunk; a 25 MiB bucket has 400 chunks
     assert nf.nf_pass1_chunk_elems(16, 6_553_600 * 201, 6_553_600) == (16_384, 400)
