@@ -182,7 +182,8 @@ inline int64_t gradient_bytes(const Geometry& g) { return 4 * (int64_t)g.W * g.n
 // kOneLaunchChunks) the slowest of them holds up each launch: there by rows
 // takes 45 to 64% of the time on conv (17 workers 6 GB 2.85 -> 1.28 ms, 32
 // workers 11.5 GB 3.76 -> 2.39) and, on runs, from 86% (48 workers, 7 GB 1.86 ->
-// 1.59) to 105% (32 workers, 11.5 GB 2.51 -> 2.64 ms).
+// 1.59) to 105% (32 workers, 9 GB 1.98 -> 2.02, 10 GB 2.28 -> 2.22, 11.5 GB 2.51
+// -> 2.64 ms).
 // FP32 sums at every position (a vetoed step) read every gradient twice by
 // rows, and still take 60 to 90% of the time through the stage: W = 16, 80 MB
 // 77 -> 54 us; 17, 1 GB 666 -> 402; 24, 9 GB 4.43 -> 3.67 ms; 48, 6 GB 3.03 ->

@@ -366,14 +366,13 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
   const int64_t gw0 = (base + e_beg) / 64;
   if (a.eg == 1) {
     // each worker's words were written by its own wavefront only
-    if (!active) return;  // 9 to 15 workers: a wavefront without one
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int j = 0; j < WPW; ++j) {
       const int w = wg + j * a.wg;
-      if (w >= R) break;
+      if (w >= R || !active) break;  // 9 to 15 workers: a wavefront without one
       for (int o = lane; o < valid; o += 64) {
         pbits[(int64_t)w * a.bstride + gw0 + o] = ppos[w * cw + o];
         nbits[(int64_t)w * a.bstride + gw0 + o] = pneg[w * cw + o];

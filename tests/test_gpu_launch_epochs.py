@@ -11,7 +11,7 @@ import torch
 import oracle as nfo
 import paper_2606_25759_amd as nf
 import synth
-from tests.nfgpu import check_decision, check_output, check_stats, oracle_policy
+from tests.nfgpu import check_decision, check_output, check_stats, oracle_policy, to_dev
 from tests.test_gpu_ternary import check_ternary_bucket, ternary_route
 
 pytestmark = pytest.mark.gpu
@@ -80,8 +80,9 @@ def test_ternary_single_launch_flat():
 
 
 def test_ternary_multi_launch():
-    # 4,273 chunks: pass 1 without sign words in five launches (1,024 chunks
-    # each at most), the plane pack in seventeen (256 at most)
+    # 4,273 chunks: the route packs the planes in its one read, in one launch;
+    # alone, pass 1 without sign words (nf_bucket_health) runs in five launches
+    # (1,024 chunks each at most) and the plane pack in seventeen (256 at most)
     W, n = 16, 70_000_000
     assert nf.nf_pass1_launches(W, n, n, sign_words=False) == 5
     assert nf.nf_pass1_launches(W, n, n) == 17
@@ -91,3 +92,14 @@ def test_ternary_multi_launch():
     pol = nf.policy(format=nf.NF_FORMAT_TERNARY, tau=0.5)
     res = ternary_route(g, mask, n, pol, bucket_n=n)
     check_ternary_bucket(res, g, mask, n, pol, 0, n, "ternary 4,273 chunks")
+    assert nf.nf_pass1_path(W, n, n, pol.format) == nf.NF_PASS1_PLANES
+    # alone, from the thresholds that the checked statistics give
+    ne = int(res["dec"][0]["n_eligible"])
+    gd, md = to_dev(g), to_dev(mask, torch.int64)
+    stats = torch.zeros(W * nf.STATS_BYTES, dtype=torch.uint8, device="cuda:0")
+    nf.nf_bucket_health(gd, n, md, stats, nf.empty_workspace(nf.nf_workspace_bytes(W, n)))
+    check_stats(nf.stats_host(stats, W)[0], res["stats"][0], "health alone", exact_abs=True)
+    theta = np.float32(0.5) * (res["stats"][0]["sum_abs_elig"] / ne).astype(np.float32)
+    bits = torch.zeros((2 * W, (n + 63) // 64), dtype=torch.int64, device="cuda:0")
+    nf.nf_pack_ternary(gd, n, md, to_dev(theta), bits)
+    assert np.array_equal(bits.cpu().numpy().view(np.uint64), res["bits"][:, : (n + 63) // 64])

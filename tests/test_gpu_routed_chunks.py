@@ -1,8 +1,9 @@
 """Pass-1 chunks whose elements are all routed to FP32, with more than 16
 workers (several workers per wavefront).  Such a chunk is read element-major
 in groups of workers, each lane keeping its running FP32 sums from one group
-to the next.  The sizes give more than 1,024 chunks, so every chunk has its
-full number of tiles (up to 16 steps of 64 elements per wavefront).  Long
+to the next.  The sizes give more than 1,024 chunks and go by tiles, so every
+chunk has its full number of tiles (up to 16 steps of 64 elements per
+wavefront).  Long
 FP32 runs hold whole routed chunks; non-finite values sit inside them, in
 workers of the first, a middle and the last group.  Every output is checked
 against the oracle: statistics, decision, sign words, counts and values."""
@@ -31,7 +32,8 @@ def routed_chunks(m, n, chunk):
 def test_routed_chunks_wide(W):
     # the library's own chunk size for a problem this large (its geometry query)
     chunk, _ = nf.nf_pass1_chunk_elems(W, 1 << 30, 1 << 30)
-    n = 1040 * chunk + 777
+    n = max(1040, (1 << 30) // (4 * W * chunk) + 1) * chunk + 777  # above the sizes that go by rows
+    assert not nf.nf_pass1_path(W, n, n) & nf.NF_PASS1_ROWS
     got, per_bucket = nf.nf_pass1_chunk_elems(W, n, n)
     assert got == chunk and per_bucket == -(-n // chunk) > 1024, (got, per_bucket)
     lay = synth.small(W, n, 4000 + W, elig_frac=0.5, nruns=40)

@@ -5,6 +5,8 @@ size and the first above it, the most partials a read-side block reduces, row
 groups above 64 workers, and every route.  Bits, counts, routes and FP32 sums
 bit for bit against the oracle; the FP64 sums and the scale within the bars of
 nfgpu (another order of exact FP64 sums; |g| sums exact without sign words)."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 
@@ -33,8 +35,11 @@ def case(W, n, seed, elig=0.85):
 EDGES = [(W, n) for W in (1, 3, 9, 16, 17, 64, 65, 255) for n in (1, 64, 511, 513, 4095, 20_001)]
 # the last small size and the first above it; 256 chunks of 64 workers are too many partials for the fused decision
 EDGES += [(W, 1024 * tile(W) + d) for W in (2, 16, 33, 64, 130) for d in (0, 1)]
-# by rows below the limits, by tiles above
+# the largest by rows up to 16 workers, the smallest by tiles, a middling one by rows
 EDGES += [(12, MB160 // 48), (8, MB160 // 32 + 1), (40, 1_500_000)]
+# the largest by rows above 16 workers and the smallest by tiles; 17 to 64 workers by rows again above 4,096 chunks
+LIMITS = [(24, GB1 // 96, True), (24, GB1 // 96 + 1, False), (70, GB1 // 280, True), (70, GB1 // 280 + 1, False),
+          (17, 4096 * 8192 - 1, False), (17, 4096 * 8192 + 1, True)]
 
 
 @pytest.mark.parametrize("W,n", EDGES)
@@ -43,6 +48,17 @@ def test_low_bit_and_vetoed(W, n):
     k = Bucket(g, mask, n)
     for pol in (nf.policy(), nf.policy(veto=1, fp32_op=nf.NF_FP32_MEAN)):
         check_route(k.route(pol), g, mask, n, pol, what=f"W={W} n={n} veto={pol.veto}")
+
+
+@pytest.mark.parametrize("W,n,by_rows", LIMITS)
+def test_limits_above_16_workers(W, n, by_rows):
+    assert bool(nf.nf_pass1_path(W, n, n) & nf.NF_PASS1_ROWS) == by_rows
+    g, mask = case(W, n, W + n)
+    k = Bucket(g, mask, n)
+    pols = (nf.policy(), nf.policy(veto=1, fp32_op=nf.NF_FP32_MEAN))
+    res = [k.route(pol) for pol in pols]
+    with ThreadPoolExecutor(2) as ex:  # the oracle's calls release the interpreter lock
+        list(ex.map(lambda i: check_route(res[i], g, mask, n, pols[i], what=f"W={W} n={n} veto={i}"), range(2)))
 
 
 @pytest.mark.parametrize("W,n", [(W, n) for W in (1, 3, 9, 16, 17, 64, 65) for n in (1, 64, 513, 20_001)] +
