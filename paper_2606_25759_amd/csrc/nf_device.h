@@ -335,9 +335,9 @@ __device__ __forceinline__ void lanes_from_ballots(const uint64_t (&bb)[NW], uin
   }
 }
 
+// A wavefront-uniform value held in a vector register, as a scalar.
 __device__ __forceinline__ int uniform32(int x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// A wavefront-uniform 64-bit value held in a vector register, as a scalar.
+__device__ __forceinline__ float uniform32(float x) { return __uint_as_float((uint32_t)uniform32((int)__float_as_uint(x))); }
 __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));

@@ -476,9 +476,9 @@ enum Pass2Op { kOpCountDecode = 0, kOpFp32 = 1, kOpFromDecision = 2, kOpFallback
 // g*g, or -1 for a worker whose sample is all zeros or holds a non-finite
 // value; ahead (in the first worker's window) is 1 if there is a -1 or the
 // norms of the sample differ by sqrt(2) kappa, and then pass 1 packs nothing
-// of the bucket.  Up to 64 workers it also turns 1 wherever pass 1 meets a
-// non-finite value: chunks that start later pack no planes.  Should the
-// bucket take the low-bit route all the same, all its rows are packed anew.
+// of the bucket.  It also turns 1 wherever pass 1 meets a non-finite value:
+// chunks that start later pack no planes.  Should the bucket take the low-bit
+// route all the same, all its rows are packed anew.
 struct Window {
   float lo, hi, power, ahead;
 };

@@ -37,7 +37,7 @@ template <int WPW, bool PACK, bool TERN, bool LOOK>
 __device__ __forceinline__ void pass1_chunk(
     const float* __restrict__ g, const uint64_t* __restrict__ mask, uint64_t* __restrict__ bits,
     float* __restrict__ out, Partial* __restrict__ part, uint64_t* __restrict__ part_ne, const Pass1Args& a,
-    int64_t q) {
+    int64_t q, float touched = 0.0f) {
   constexpr int NW = pass1_words(WPW);
   extern __shared__ __align__(16) unsigned char smem[];
   // chunk q -> bucket b, chunk c within it; the chunk's partials go to slot q
@@ -98,7 +98,7 @@ __device__ __forceinline__ void pass1_chunk(
     for (int j = 0; j < WPW; ++j) {
       const int w = wg + j * a.wg;
       const Window wd = load_window(a.win, (int64_t)b * a.wtot + (w < a.W ? w : wg));
-      wdr[j] = float2{wd.lo, wd.hi};
+      wdr[j] = float2{uniform32(wd.lo), uniform32(wd.hi)};
     }
   }
   // Word k of this lane's NW of worker w's planes from word `at` of the chunk on.
@@ -212,6 +212,8 @@ __device__ __forceinline__ void pass1_chunk(
     }
   }
 
+  // k_pass1's touch of the first tile is in by now.
+  if (WPW == 4 && !PACK) asm volatile("" ::"v"(touched));
   // G-Ternary: no planes in a bucket that falls back (see Window), the same in
   // all wavefronts of the block.
   const bool drop = LOOK && __builtin_amdgcn_readfirstlane((int)ahead_s) != 0;
@@ -738,7 +740,7 @@ __device__ __forceinline__ void pass1_chunk(
   }
 
   // the chunks that start from now on (see Window)
-  if (LOOK && a.ratio >= 0.0f) {
+  if (TERN && a.ratio >= 0.0f) {
     uint64_t some = 0;
 #pragma unroll
     for (int j = 0; j < WPW; ++j) some |= nonf[j];
@@ -845,10 +847,15 @@ __device__ __forceinline__ void pass1_chunk(
 // G-Ternary with four workers per wavefront: the loops have no register left
 // for the flag (14 spilled, and an ordinary step of 128 workers, 8 GB took
 // 3.08 ms instead of 2.62; with the windows in LDS none, but 2.71), so a block
-// runs one of two codes by what the sample foretold.  That does not change
-// while pass 1 runs, so every wavefront reads the same.  A fallback of 128
-// workers, 8 GB takes 2.90 ms (3.53 with planes packed all the same, 2.86 with
-// two reads), an ordinary step 2.67 (2.65 without the choice).
+// runs one of two codes by what the flag says at its start, read once for the
+// block: the two do not meet at the same barriers.  Before that barrier each
+// thread touches a line of the chunk's first tile, or the flag's way from the
+// L2 adds to every chunk (1% of an ordinary step); after it, the compiler no
+// longer loads the windows into scalars by itself (in vector registers they
+// spilled 20, and an ordinary step took 3.28 ms).  128 workers, 8 GB, a fallback
+// by infinities that the sample missed: 3.53 -> 2.84 ms (2.85 with two reads);
+// ordinary steps 2.64 -> 2.62, 255 workers 2.84 -> 2.80, 200 workers, 4 GB 1.62 ->
+// 1.64.
 template <int WPW, bool PACK, bool TERN>
 __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <= 2 && PACK ? 8 : 4, WPW <= 2 && PACK ? 8 : 4))) void k_pass1(
     const float* __restrict__ g, const uint64_t* __restrict__ mask, uint64_t* __restrict__ bits,
@@ -860,10 +867,22 @@ __global__ __launch_bounds__(kThreads1) __attribute__((amdgpu_waves_per_eu(WPW <
     int b;
     int64_t c;
     chunk_home(q, a.btab, a.cbucket, a.nb, a.chunks_full, b, c);
-    if (uniform32((int)(load_window(a.win0, (int64_t)b * a.wtot).ahead != 0.0f)))
-      pass1_chunk<WPW, false, false, false>(g, mask, bits, out, part, part_ne, a, q);
+    int64_t base, nbe, chunk0;
+    bucket_span(b, a.btab, a.n_total, a.bucket_n, a.slots, base, nbe, chunk0);
+    __shared__ uint32_t foretold;
+    float ahead = 0.0f;
+    if (threadIdx.x == 0) ahead = load_ahead(a.win0 + (int64_t)b * a.wtot);
+    constexpr int LINES = pass1_words(WPW) * 4;  // 64-byte pieces of a worker's row of a tile
+    const int row = threadIdx.x / LINES;
+    int64_t e = c * a.G * a.T + 16 * (threadIdx.x % LINES);
+    if (e >= nbe) e = nbe - 1;
+    const float touched = g[(int64_t)(row < a.W ? row : 0) * a.wstride + base + e];
+    if (threadIdx.x == 0) foretold = ahead != 0.0f;
+    __syncthreads();
+    if (uniform32((int)foretold))
+      pass1_chunk<WPW, false, false, false>(g, mask, bits, out, part, part_ne, a, q, touched);
     else
-      pass1_chunk<WPW, false, true, false>(g, mask, bits, out, part, part_ne, a, q);
+      pass1_chunk<WPW, false, true, false>(g, mask, bits, out, part, part_ne, a, q, touched);
   } else {
     pass1_chunk<WPW, PACK, TERN, TERN>(g, mask, bits, out, part, part_ne, a, q);
   }

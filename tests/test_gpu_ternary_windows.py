@@ -104,3 +104,13 @@ def test_foretold_fallback(kind, W, n):
     else:
         assert route == nfo.ROUTE_F
         assert (res["bits"] == ~np.uint64(0)).all()
+
+
+@pytest.mark.parametrize("W,n", [(8, BYTES // 32 + 77), (20, GIB // 80 + 4099), (70, GIB // 280 + 4099)])
+def test_fallback_met_while_reading(W, n):
+    """One infinity, which the sample misses: some chunks have packed planes when pass 1 meets it, later ones do not."""
+    g, mask = data(W, n, n)
+    g[W // 3, n // 4] = np.inf
+    pol = nf.policy(format=nf.NF_FORMAT_TERNARY)
+    res = ternary_route(g, mask, n, pol)
+    assert check_ternary_bucket(res, g, mask, n, pol, 0, n, f"W={W}") == nfo.ROUTE_F

@@ -52,13 +52,25 @@ def ptr(a):
 PARTIAL = np.dtype([("sabs", "f8"), ("ssq", "f8"), ("nonfinite", "u8"), ("sabs_c", "f8"), ("sabs_b", "f8")])
 
 
-# tiles of 1,024 elements at 8 workers (two element groups), 2,048 at 4, 512 at 9 and 16 (one group): chunks that are
-# all eligible, mixed, all FP32, and a ragged last one
+# tiles of 1,024 elements at 8 workers (two element groups), 2,048 at 4, 512 at 9 and 16 (one group), 256 at 70 (two
+# row groups, four workers a wavefront): chunks that are all eligible, mixed, all FP32, and a ragged last one
 @pytest.mark.parametrize("turn", [0, 1, 7, 8, 15, 16])
-@pytest.mark.parametrize("W", [4, 8, 9, 16])
+@pytest.mark.parametrize("W", [4, 8, 9, 16, 70])
 def test_flag_turns_between_wavefronts(lib, W, turn):
-    tile = (16 // W) * 512
-    G, n = 2, 7 * tile + 333
+    found = run_planes(lib, W, turn, None)
+    assert not found
+
+
+@pytest.mark.parametrize("W,bad", [(8, 3), (16, 15), (70, 2), (70, 69)])
+def test_nonfinite_value_sets_the_flag(lib, W, bad):
+    """Chunks that start later then pack no planes."""
+    assert run_planes(lib, W, 16, bad)
+
+
+def run_planes(lib, W, turn, bad):
+    """Pass 1 over a bucket, everything checked; worker `bad` has an infinity.  Returns whether the flag was set."""
+    tile = (16 // W) * 512 if W <= 16 else 256
+    G, n = 2, 7 * tile + 333 % tile
     rng = np.random.default_rng(W)
     g = rng.standard_normal((W, n)).astype(np.float32)
     words = (n + 63) // 64
@@ -66,6 +78,8 @@ def test_flag_turns_between_wavefronts(lib, W, turn):
     el[2 * tile + 70:2 * tile + 700] = False  # second chunk: mixed
     el[4 * tile:6 * tile] = False  # third: FP32
     el[n:] = False
+    if bad is not None:
+        g[bad, tile + 5] = np.inf
     mask = np.packbits(el, bitorder="little").view(np.uint64).copy()
     chunks = -(-n // (G * tile))
     bits = np.full((2 * W, words), 0x5555, np.uint64)
@@ -84,9 +98,10 @@ def test_flag_turns_between_wavefronts(lib, W, turn):
         s = slice(c * G * tile, min((c + 1) * G * tile, n))
         assert part_ne[c] == el[s].sum()
         x = g[:, s].astype(np.float64)
-        np.testing.assert_allclose(part["sabs"][c] + part["sabs_c"][c], np.abs(x[:, el[s]]).sum(1), rtol=1e-14)
+        np.testing.assert_allclose(part["sabs"][c] + part["sabs_c"][c] if bad is None else part["sabs"][c],
+                                   np.abs(x[:, el[s]]).sum(1), rtol=1e-14)
         np.testing.assert_allclose(part["ssq"][c], (x * x).sum(1), rtol=1e-13)  # 4,096 terms in another order
-        assert not part["nonfinite"][c].any()
+        assert np.array_equal(part["nonfinite"][c], (~np.isfinite(x)).sum(1))
     want = g[0].copy()
     for w in range(1, W):
         want = want + g[w]
@@ -96,3 +111,6 @@ def test_flag_turns_between_wavefronts(lib, W, turn):
         planes = np.concatenate([keep & (g > 0), keep & (g < 0)])
         planes = np.pad(planes, ((0, 0), (0, words * 64 - n)))
         assert np.array_equal(np.packbits(planes, axis=1, bitorder="little").view(np.uint64), bits)
+    if turn == 0:  # the whole block did
+        assert (bits == 0x5555).all()
+    return win[0, 3] != 0
