@@ -824,7 +824,7 @@ def main():
 
     # HBM bytes per pass-1 launch from the committed counters (null unless taken on this kernel source)
     if args.ddp_buckets:
-        traffic = None if ternary else pass1_traffic(committed_counters(name, "ddp"))
+        traffic = None if ternary else pass1_traffic(committed_counters(name, "ddp"), m["pass1"]["kernel"])
     else:
         traffic = counter_traffic(name) if not ternary else None
     roofline = dict(m["pass1"])
