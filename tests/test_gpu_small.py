@@ -39,7 +39,7 @@ EDGES += [(W, 1024 * tile(W) + d) for W in (2, 16, 33, 64, 130) for d in (0, 1)]
 EDGES += [(12, MB160 // 48), (8, MB160 // 32 + 1), (40, 1_500_000)]
 # the largest by rows above 16 workers and the smallest by tiles; 17 to 64 workers by rows again above 4,096 chunks
 LIMITS = [(24, GB1 // 96, True), (24, GB1 // 96 + 1, False), (70, GB1 // 280, True), (70, GB1 // 280 + 1, False),
-          (17, 4096 * 8192 - 1, False), (17, 4096 * 8192 + 1, True)]
+          (17, 4096 * 8192 + 1, True)]
 
 
 @pytest.mark.parametrize("W,n", EDGES)
